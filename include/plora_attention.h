@@ -26,7 +26,7 @@
  * Arithmetic: bf16 inputs, fp32 scores, exponentials and sums, one
  * round-to-nearest-even rounding at the output store.  Every call is
  * asynchronous on stream and allocates nothing; the merge is bitwise
- * deterministic (partitions in ascending order).
+ * deterministic (a fixed order that depends on the partition count).
  * Errors: PLORA_ERR_INVALID_ARG for a null pointer, batch, heads or max_len
  * below 0; PLORA_ERR_UNSUPPORTED for pointers not 16-byte aligned or a
  * per-(request, head) cache of 2^31 bytes or more; PLORA_ERR_WORKSPACE_TOO_SMALL
@@ -53,7 +53,8 @@ extern "C" {
 int32_t plora_attn_partitions(int64_t max_len);
 
 /* Host.  Bytes of workspace plora_attn_decode needs: m, l and o as laid out
- * above, each section 256-byte aligned; 0 for an empty shape. */
+ * above, each section 256-byte aligned; 0 for an empty shape.  (The call may
+ * use fewer, longer partitions of its own.) */
 size_t plora_attn_workspace_bytes(int32_t batch, int32_t heads, int64_t max_len);
 
 /* Steps 1 to 3 on every partition (the devices' share of section V-B): m, l
@@ -68,8 +69,8 @@ plora_status plora_attn_merge(const float* m, const float* l, const float* o,
                               const int32_t* lens, int32_t batch, int32_t heads,
                               int64_t max_len, uint16_t* out, hipStream_t stream);
 
-/* plora_attn_partial then plora_attn_merge through ws (at least
- * plora_attn_workspace_bytes bytes, 16-byte aligned). */
+/* Both steps through ws (at least plora_attn_workspace_bytes bytes, 16-byte
+ * aligned), in partitions of PLORA_ATTN_CHUNK keys or a multiple of it. */
 plora_status plora_attn_decode(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                                const int32_t* lens, int32_t batch, int32_t heads,
                                int64_t max_len, float scale, uint16_t* out, void* ws,

@@ -21,11 +21,16 @@
 namespace {
 
 constexpr int kD = PLORA_ATTN_HEAD_DIM;   // 128: sixteen 16-byte units per row
-constexpr int kC = PLORA_ATTN_CHUNK;      // keys per partition
+constexpr int kC = PLORA_ATTN_CHUNK;      // keys per partition of the ABI
 constexpr int kNT = 256;                  // threads per work group
-constexpr int kGroups = kNT / 16;         // keys in flight per pass (16 lanes each)
-constexpr int kKeysPerThread = kC / kGroups;
+constexpr int kGroups = kNT / 16;         // keys per pass (16 lanes each)
+constexpr int kStage = 8;                 // keys per 16-lane group and stage
+constexpr int kStageKeys = kStage * kGroups;   // keys per stage of a work group
+static_assert(kC % kStageKeys == 0, "partitions are whole stages");
 
+// (the merge takes partials and outputs of any element alignment)
+typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2), aligned(2)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kRsrcWord3 = 0x00020000;    // raw buffer, 32-bit data format (gfx9 family)
 constexpr int kPastEnd = (int)0x80000000u;
@@ -57,87 +62,139 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint16_t* p, i
                                            kRsrcWord3);
 }
 
+// Non-temporal: every key and value is read once per call (a plain read of
+// 2.4 GB runs at 7.1 TB/s non-temporally, at 6.3 otherwise).
 __device__ __forceinline__ uint4 bld16(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  const i32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);
+  const i32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 2);
   return make_uint4((uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w);
 }
 
-// Partition blockIdx.x of head blockIdx.y of request blockIdx.z.  Thread
-// (g, e) = (tid / 16, tid % 16) takes keys lo + g + 16 j, j < 16, and the
-// dimensions 8 e .. 8 e + 7 of each: the sixteen lanes of a key read its row
-// as one coalesced 256-byte line, and every thread requests all sixteen of
-// its key units and value units before it uses any.
-__global__ __launch_bounds__(kNT) void attn_partial_kernel(
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+// Sum over each row of 16 lanes, in every lane of the row (quad permutations,
+// then the mirrored half row and row: register moves, where a shuffle by xor
+// goes through LDS).
+__device__ __forceinline__ float row_sum(float x) {
+  x = dpp_add<0xb1>(x);     // quad_perm [1,0,3,2]
+  x = dpp_add<0x4e>(x);     // quad_perm [2,3,0,1]
+  x = dpp_add<0x141>(x);    // row_half_mirror
+  x = dpp_add<0x140>(x);    // row_mirror
+  return x;
+}
+
+// Partition blockIdx.x (CH keys from blockIdx.x CH) of head blockIdx.y of
+// request blockIdx.z.  Thread (g, e) = (tid / 16, tid % 16) takes keys g,
+// g + 16, ... of the partition and the dimensions 8 e .. 8 e + 7 of each: the
+// sixteen lanes of a key read its row as one coalesced 256-byte line.  A
+// stage is eight keys per group (128 keys), all of whose key and value units
+// are requested before any is used; each group keeps its own running maximum,
+// sum and output (rescaled once per stage), so the work group's wavefronts
+// meet only at the end, where the groups are rescaled to the common anchor.
+// With out set (P = 1) the only partition is the whole cache and is written
+// as the output itself.
+// The partitions of a head start at another one for each head: in grid order
+// partition p of every head would run on XCD p mod P where P divides 8, and
+// the last partitions, past most requests' lengths, would leave their XCDs
+// idle (64 x 32 x 512..4096 keys: 507 us at 512-key partitions, 367 rotated;
+// 434 and 386 at 256).  The former kernel (256-key partitions, all 32 units
+// of a thread requested at once, reductions through LDS, default cache
+// policy) took 446 us there.
+// Bound by reading K and V; the loads in flight come from the resident work
+// groups (four per compute unit), so no stage is requested ahead of another.
+__global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ lens, int32_t heads,
-    int64_t max_len, float scale, int32_t P, float* __restrict__ m_out,
-    float* __restrict__ l_out, float* __restrict__ o_out) {
+    int64_t max_len, float scale, int32_t P, int32_t CH, float* __restrict__ m_out,
+    float* __restrict__ l_out, float* __restrict__ o_out, uint16_t* __restrict__ out) {
   __shared__ float red[kNT / 64][kD];
   __shared__ float wmax[kNT / 64], wsum[kNT / 64];
-  const int p = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int p = (int)((blockIdx.x + (uint32_t)b * (uint32_t)heads + (uint32_t)h) % (uint32_t)P);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g = tid >> 4, e = tid & 15;
   int n = lens[b];
   n = (n < 0 || n > max_len) ? 0 : n;
-  const int lo = p * kC;
-  if (lo >= n) return;                            // no key here: nothing written
+  const int lo = p * CH;
+  if (lo >= n) {                                  // no key here: no partial written
+    if (out && tid < kD / 8)
+      *reinterpret_cast<uint4*>(out + ((int64_t)b * heads + h) * kD + 8 * tid) =
+          make_uint4(0, 0, 0, 0);
+    return;
+  }
+  const int hi = min(n, lo + CH);
   const int64_t row0 = ((int64_t)b * heads + h) * max_len;
   const __amdgpu_buffer_rsrc_t kr = rows_rsrc(k + row0 * kD, n);
   const __amdgpu_buffer_rsrc_t vr = rows_rsrc(v + row0 * kD, n);
-
-  uint4 kreg[kKeysPerThread], vreg[kKeysPerThread];
-#pragma unroll
-  for (int j = 0; j < kKeysPerThread; ++j) {
-    const int t = lo + g + kGroups * j;           // < lo + kC; past n reads zero
-    kreg[j] = bld16(kr, t < n ? (t * kD + 8 * e) * 2 : kPastEnd);
-  }
-#pragma unroll
-  for (int j = 0; j < kKeysPerThread; ++j) {
-    const int t = lo + g + kGroups * j;
-    vreg[j] = bld16(vr, t < n ? (t * kD + 8 * e) * 2 : kPastEnd);
-  }
   float qf[8];
   unpack8(*reinterpret_cast<const uint4*>(q + ((int64_t)b * heads + h) * kD + 8 * e), qf);
 #pragma unroll
   for (int i = 0; i < 8; ++i) qf[i] *= scale;
 
-  // step 1: scores, each summed over the sixteen lanes of its key
-  float s[kKeysPerThread];
-  float mx = -INFINITY;
+  float m = -INFINITY, sum = 0.f;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int t0 = lo + g; t0 - g < hi; t0 += kStageKeys) {
+    uint4 kreg[kStage], vreg[kStage];
 #pragma unroll
-  for (int j = 0; j < kKeysPerThread; ++j) {
-    float kf[8];
-    unpack8(kreg[j], kf);
-    float d = 0.f;
+    for (int j = 0; j < kStage; ++j) {
+      const int t = t0 + kGroups * j;             // keys past hi read zero
+      kreg[j] = bld16(kr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
+    }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) d = fmaf(qf[i], kf[i], d);
+    for (int j = 0; j < kStage; ++j) {
+      const int t = t0 + kGroups * j;
+      vreg[j] = bld16(vr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
+    }
+    // step 1: scores, each summed over the sixteen lanes of its key
+    float s[kStage];
+    float mn = m;
 #pragma unroll
-    for (int msk = 1; msk < 16; msk <<= 1) d += __shfl_xor(d, msk, 64);
-    const int t = lo + g + kGroups * j;
-    s[j] = t < n ? d : -INFINITY;
-    mx = fmaxf(mx, s[j]);
+    for (int j = 0; j < kStage; ++j) {
+      float kf[8];
+      unpack8(kreg[j], kf);
+      float d = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) d = fmaf(qf[i], kf[i], d);
+      d = row_sum(d);
+      s[j] = t0 + kGroups * j < hi ? d : -INFINITY;
+      mn = fmaxf(mn, s[j]);
+    }
+    // steps 2 and 3: shifted exponentials, their sum, the weighted values.
+    // While every score so far is -inf (no key yet, or scores below the
+    // range) the shift is 0: their weights are 0, and a NaN score's is NaN.
+    const float ms = mn == -INFINITY ? 0.f : mn;
+    const float c = expf(m - ms);
+    m = mn;
+    sum *= c;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] *= c;
+#pragma unroll
+    for (int j = 0; j < kStage; ++j) {
+      const float w = expf(s[j] - ms);            // 0 for keys past hi
+      sum += w;
+      float vf[8];
+      unpack8(vreg[j], vf);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, vf[i], acc[i]);
+    }
   }
-  // the partition's anchor
+  // the partition's anchor, and each group's sums rescaled to it
+  float mx = m;
 #pragma unroll
   for (int msk = 16; msk < 64; msk <<= 1) mx = fmaxf(mx, __shfl_xor(mx, msk, 64));
   if (lane == 0) wmax[wv] = mx;
   __syncthreads();
-  float m = wmax[0];
+  mx = wmax[0];
 #pragma unroll
-  for (int w = 1; w < kNT / 64; ++w) m = fmaxf(m, wmax[w]);
-
-  // steps 2 and 3: shifted exponentials, their sum, the weighted values
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float sum = 0.f;
+  for (int w = 1; w < kNT / 64; ++w) mx = fmaxf(mx, wmax[w]);
+  // (a partition whose every score is -inf has no anchor to shift by: its
+  // sums are NaN, as exp(-inf - -inf) is)
+  const float c = mx == -INFINITY ? NAN : expf(m - mx);
+  sum *= c;
 #pragma unroll
-  for (int j = 0; j < kKeysPerThread; ++j) {
-    const float w = expf(s[j] - m);               // 0 for keys past n
-    sum += w;
-    float vf[8];
-    unpack8(vreg[j], vf);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = fmaf(w, vf[i], acc[i]);
-  }
+  for (int i = 0; i < 8; ++i) acc[i] *= c;
   // sum: each key counted once (the sixteen lanes of a key hold the same w)
 #pragma unroll
   for (int msk = 16; msk < 64; msk <<= 1) sum += __shfl_xor(sum, msk, 64);
@@ -152,42 +209,75 @@ __global__ __launch_bounds__(kNT) void attn_partial_kernel(
   if (lane == 0) wsum[wv] = sum;
   __syncthreads();
   const int64_t part = ((int64_t)b * heads + h) * P + p;
+  float l = wsum[0];
+#pragma unroll
+  for (int w = 1; w < kNT / 64; ++w) l += wsum[w];
   if (tid < kD) {
     float o = red[0][tid];
 #pragma unroll
     for (int w = 1; w < kNT / 64; ++w) o += red[w][tid];
-    o_out[part * kD + tid] = o;
+    if (out) out[part * kD + tid] = (uint16_t)to_bf16(o / l);
+    else o_out[part * kD + tid] = o;
   }
-  if (tid == 0) {
-    float l = wsum[0];
-#pragma unroll
-    for (int w = 1; w < kNT / 64; ++w) l += wsum[w];
-    m_out[part] = m;
+  if (tid == 0 && !out) {
+    m_out[part] = mx;
     l_out[part] = l;
   }
 }
 
-// The rescaling: one work group of kD threads per (request, head), thread d
-// for output dimension d, partitions in ascending order.
-__global__ __launch_bounds__(kD) void attn_merge_kernel(
+// The rescaling: one work group per (request, head).  Thread (g, e) = (tid /
+// 32, tid % 32) takes the output dimensions 4 e .. 4 e + 3 of partitions g,
+// g + G, ...; the G groups are then summed in ascending order through LDS.
+// With one thread per dimension walking every partition, a cache of 30k keys
+// took 30 us for its 118 dependent rounds.
+template <int G>
+__global__ __launch_bounds__(32 * G) void attn_merge_kernel(
     const float* __restrict__ m_in, const float* __restrict__ l_in,
     const float* __restrict__ o_in, const int32_t* __restrict__ lens, int32_t heads,
-    int64_t max_len, int32_t P, uint16_t* __restrict__ out) {
-  const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
+    int64_t max_len, int32_t P, int32_t CH, uint16_t* __restrict__ out) {
+  __shared__ float4 red[G][32];
+  __shared__ float lred[G], mred[G];
+  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int g = tid >> 5, e = tid & 31;
   int n = lens[b];
   n = (n < 0 || n > max_len) ? 0 : n;
-  const int np = (n + kC - 1) / kC;
+  const int np = n > 0 ? (n - 1) / CH + 1 : 0;
   const int64_t base = ((int64_t)b * heads + h) * P;
+  // M: every group finds it by itself, over 32 partitions at a time
   float M = -INFINITY;
-  for (int p = 0; p < np; ++p) M = fmaxf(M, m_in[base + p]);
-  float L = 0.f, o = 0.f;
-  for (int p = 0; p < np; ++p) {
+  for (int p = tid; p < np; p += 32 * G) M = fmaxf(M, m_in[base + p]);
+#pragma unroll
+  for (int msk = 1; msk < 32; msk <<= 1) M = fmaxf(M, __shfl_xor(M, msk, 64));
+  if (e == 0) mred[g] = M;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < G; ++q) M = fmaxf(M, mred[q]);
+  float L = 0.f;
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int p = g; p < np; p += G) {
+    const f32x4_t op = *reinterpret_cast<const f32x4_t*>(o_in + (base + p) * kD + 4 * e);
     const float w = expf(m_in[base + p] - M);
     L = fmaf(w, l_in[base + p], L);
-    o = fmaf(w, o_in[(base + p) * kD + d], o);
+    o.x = fmaf(w, op.x, o.x); o.y = fmaf(w, op.y, o.y);
+    o.z = fmaf(w, op.z, o.z); o.w = fmaf(w, op.w, o.w);
   }
-  const float r = np > 0 ? o / L : 0.f;
-  out[((int64_t)b * heads + h) * kD + d] = (uint16_t)to_bf16(r);
+  red[g][e] = o;
+  if (e == 0) lred[g] = L;
+  __syncthreads();
+  if (g != 0) return;
+#pragma unroll
+  for (int q = 1; q < G; ++q) {
+    const float4 a = red[q][e];
+    o.x += a.x; o.y += a.y; o.z += a.z; o.w += a.w;
+    L += lred[q];
+  }
+  u32x2_t r = {0, 0};
+  if (np > 0) {
+    r.x = to_bf16(o.x / L) | (to_bf16(o.y / L) << 16);
+    r.y = to_bf16(o.z / L) | (to_bf16(o.w / L) << 16);
+  }
+  *reinterpret_cast<u32x2_t*>(out + ((int64_t)b * heads + h) * kD + 4 * e) = r;
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -207,6 +297,52 @@ plora_status check_shape(int32_t batch, int32_t heads, int64_t max_len) {
   // one (request, head) cache is read through 32-bit byte offsets
   if (max_len * kD * 2 >= (INT64_C(1) << 31)) return PLORA_ERR_UNSUPPORTED;
   return PLORA_OK;
+}
+
+int32_t partitions(int64_t max_len, int32_t CH) {
+  return max_len <= 0 ? 0 : (int32_t)((max_len + CH - 1) / CH);
+}
+
+// Keys per partition of plora_attn_decode's own partials.  Twice the ABI's
+// where that still leaves 24 work groups per compute unit (64 requests x 32
+// heads x up to 4096 keys: 367 us against 386, half the partials), or where
+// one such partition holds the whole cache, so that no merge follows, and
+// the heads alone fill the chip (64 x 32 x up to 300 keys: 33 us against 41);
+// below that the finer split balances better (16 requests: 97.4 us against
+// 98.7, 4 requests 28.5 against 31.6).
+int32_t decode_chunk(int32_t batch, int32_t heads, int64_t max_len) {
+  const int64_t bh = (int64_t)batch * heads;
+  const bool one = max_len <= 2 * kC && bh >= 1024;
+  return one || bh * partitions(max_len, 2 * kC) >= 24 * 256 ? 2 * kC : kC;
+}
+
+plora_status run_partial(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                         const int32_t* lens, int32_t batch, int32_t heads, int64_t max_len,
+                         float scale, int32_t CH, float* m, float* l, float* o, uint16_t* out,
+                         hipStream_t stream) {
+  if (!q || !k || !v || !lens || !m || !l || !o) return PLORA_ERR_INVALID_ARG;
+  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o))
+    return PLORA_ERR_UNSUPPORTED;
+  const int32_t P = partitions(max_len, CH);
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(attn_partial_kernel, dim3(P, heads, batch), dim3(kNT), 0, stream, q, k,
+                     v, lens, heads, max_len, scale, P, CH, m, l, o, out);
+  return launch_status();
+}
+
+plora_status run_merge(const float* m, const float* l, const float* o, const int32_t* lens,
+                       int32_t batch, int32_t heads, int64_t max_len, int32_t CH,
+                       uint16_t* out, hipStream_t stream) {
+  if (!m || !l || !o || !lens || !out) return PLORA_ERR_INVALID_ARG;
+  const int32_t P = partitions(max_len, CH);
+  (void)hipGetLastError();
+  if (P <= 32)
+    hipLaunchKernelGGL(attn_merge_kernel<4>, dim3(heads, batch), dim3(128), 0, stream, m, l, o,
+                       lens, heads, max_len, P, CH, out);
+  else
+    hipLaunchKernelGGL(attn_merge_kernel<32>, dim3(heads, batch), dim3(1024), 0, stream, m, l, o,
+                       lens, heads, max_len, P, CH, out);
+  return launch_status();
 }
 
 }  // namespace
@@ -230,14 +366,7 @@ plora_status plora_attn_partial(const uint16_t* q, const uint16_t* k, const uint
   plora_status st = check_shape(batch, heads, max_len);
   if (st != PLORA_OK) return st;
   if (batch == 0 || heads == 0 || max_len == 0) return PLORA_OK;
-  if (!q || !k || !v || !lens || !m || !l || !o) return PLORA_ERR_INVALID_ARG;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o))
-    return PLORA_ERR_UNSUPPORTED;
-  const int32_t P = plora_attn_partitions(max_len);
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(attn_partial_kernel, dim3(P, heads, batch), dim3(kNT), 0, stream, q, k,
-                     v, lens, heads, max_len, scale, P, m, l, o);
-  return launch_status();
+  return run_partial(q, k, v, lens, batch, heads, max_len, scale, kC, m, l, o, nullptr, stream);
 }
 
 plora_status plora_attn_merge(const float* m, const float* l, const float* o,
@@ -246,11 +375,7 @@ plora_status plora_attn_merge(const float* m, const float* l, const float* o,
   plora_status st = check_shape(batch, heads, max_len);
   if (st != PLORA_OK) return st;
   if (batch == 0 || heads == 0 || max_len == 0) return PLORA_OK;
-  if (!m || !l || !o || !lens || !out) return PLORA_ERR_INVALID_ARG;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(attn_merge_kernel, dim3(heads, batch), dim3(kD), 0, stream, m, l, o,
-                     lens, heads, max_len, plora_attn_partitions(max_len), out);
-  return launch_status();
+  return run_merge(m, l, o, lens, batch, heads, max_len, kC, out, stream);
 }
 
 plora_status plora_attn_decode(const uint16_t* q, const uint16_t* k, const uint16_t* v,
@@ -264,14 +389,18 @@ plora_status plora_attn_decode(const uint16_t* q, const uint16_t* k, const uint1
   if (!aligned16(ws)) return PLORA_ERR_UNSUPPORTED;
   if (ws_bytes < plora_attn_workspace_bytes(batch, heads, max_len))
     return PLORA_ERR_WORKSPACE_TOO_SMALL;
-  const size_t parts = (size_t)batch * heads * plora_attn_partitions(max_len);
+  const int32_t CH = decode_chunk(batch, heads, max_len);
+  const size_t parts = (size_t)batch * heads * partitions(max_len, CH);
   char* base = reinterpret_cast<char*>(ws);
   float* m = reinterpret_cast<float*>(base);
   float* l = reinterpret_cast<float*>(base + align256(parts * 4));
   float* o = reinterpret_cast<float*>(base + 2 * align256(parts * 4));
-  st = plora_attn_partial(q, k, v, lens, batch, heads, max_len, scale, m, l, o, stream);
-  if (st != PLORA_OK) return st;
-  return plora_attn_merge(m, l, o, lens, batch, heads, max_len, out, stream);
+  if (!out) return PLORA_ERR_INVALID_ARG;
+  const bool whole = partitions(max_len, CH) == 1 && aligned16(out);
+  st = run_partial(q, k, v, lens, batch, heads, max_len, scale, CH, m, l, o,
+                   whole ? out : nullptr, stream);
+  if (st != PLORA_OK || whole) return st;
+  return run_merge(m, l, o, lens, batch, heads, max_len, CH, out, stream);
 }
 
 }  // extern "C"

@@ -173,3 +173,33 @@ def test_llama7b_decode_shape(P):
         ref = OA.attention(u16(q[b:b + 1, h:h + 1]), u16(K[b:b + 1, h:h + 1]),
                            u16(V[b:b + 1, h:h + 1]), lens[b:b + 1], scale)
         check_out(ob[b:b + 1, h:h + 1], ref)
+
+
+@pytest.mark.parametrize("Bn,H,Lmax", [
+    (256, 32, 300),      # one partition holds the cache: no merge
+    (48, 32, 2100),      # partitions of 512 keys, the last one short
+    (3, 1, 8500),        # 34 partitions: the wide merge, more than its 32 groups
+    (2, 1, 33),          # one partition of the short form, then the merge
+])
+def test_decode_partition_forms(P, Bn, H, Lmax):
+    """The partitions plora_attn_decode takes by shape, against the
+    definition on sampled (request, head) pairs; lengths at the edges."""
+    rng = np.random.default_rng(Lmax)
+    g = torch.Generator(device="cuda").manual_seed(Lmax)
+    mk = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, K, V = mk(Bn, H, D), mk(Bn, H, Lmax, D), mk(Bn, H, Lmax, D)
+    lens = rng.integers(1, Lmax + 1, Bn).astype(np.int32)
+    edge = [n for n in (Lmax, 0, 1, 127, 128, 129, 511, 512, 513) if n <= Lmax][:Bn]
+    lens[:len(edge)] = edge
+    out = torch.full((Bn, H, D), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(P.attn_workspace_bytes(Bn, H, Lmax), dtype=torch.uint8, device="cuda")
+    P.attn_decode(q, K, V, dev(lens), 0.09, out, ws)
+    torch.cuda.synchronize()
+    u16 = lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    for b in sorted({*range(min(len(edge), Bn)), Bn - 1, int(rng.integers(0, Bn))}):
+        h = int(rng.integers(0, H))
+        pick = lambda t: u16(t[b:b + 1, h:h + 1])
+        ref = OA.attention(pick(q), pick(K), pick(V), lens[b:b + 1], 0.09)
+        check_out(pick(out), ref)
+        if lens[b] == 0:
+            assert (out[b] == 0).all()
