@@ -306,14 +306,14 @@ int32_t partitions(int64_t max_len, int32_t CH) {
 // Keys per partition of plora_attn_decode's own partials.  Twice the ABI's
 // where that still leaves 24 work groups per compute unit (64 requests x 32
 // heads x up to 4096 keys: 367 us against 386, half the partials), or where
-// one such partition holds the whole cache, so that no merge follows, and
-// the heads alone fill the chip (64 x 32 x up to 300 keys: 33 us against 41);
-// below that the finer split balances better (16 requests: 97.4 us against
-// 98.7, 4 requests 28.5 against 31.6).
+// one such partition holds the whole cache, so that no merge follows (26 x 16
+// x up to 464 keys: 16.1 us against 20.1; 64 x 32 x 300: 29 against 41; a
+// single request 8.3 against 11.0); below that the finer split balances
+// better (16 requests of 4096: 97.4 us against 98.7, 4 requests 28.5 against
+// 31.6).
 int32_t decode_chunk(int32_t batch, int32_t heads, int64_t max_len) {
-  const int64_t bh = (int64_t)batch * heads;
-  const bool one = max_len <= 2 * kC && bh >= 1024;
-  return one || bh * partitions(max_len, 2 * kC) >= 24 * 256 ? 2 * kC : kC;
+  const int64_t groups = (int64_t)batch * heads * partitions(max_len, 2 * kC);
+  return max_len <= 2 * kC || groups >= 24 * 256 ? 2 * kC : kC;
 }
 
 plora_status run_partial(const uint16_t* q, const uint16_t* k, const uint16_t* v,
