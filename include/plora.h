@@ -137,10 +137,11 @@ typedef enum {
  *               offset is negative.
  * Appended fields default to zero in C aggregate initialisation, so callers
  * without pools need not set them.
- * Ranks that are multiples of 8 run the vector and matrix-core paths of the
- * next power of two with their own row stride; other ranks (rows of A_i
- * that are not 16-byte aligned) take an LDS-staged shrink, correct but not
- * tuned.  Offsets are multiples of 8 for every rank when h_in and h_out
+ * For batches above 256 tokens, ranks that are multiples of 8 run the vector
+ * and matrix-core paths of the next power of two with their own row stride,
+ * and other ranks (rows of A_i that are not 16-byte aligned) take an
+ * LDS-staged shrink, correct but not tuned; smaller batches stream A_i as one
+ * run of 16-byte chunks whatever the rank.  Offsets are multiples of 8 for every rank when h_in and h_out
  * are, as back-to-back blocks give.
  */
 typedef struct {
@@ -255,8 +256,8 @@ plora_status plora_segment(const int32_t* idx, const plora_segments* seg,
  * (the rank-r reduction m = xA of strategy E4, section V-A).  Entries of v
  * for other tokens and columns are not written.  Two launches: the partial
  * sums over slices of h_in into ws (at least plora_workspace_bytes(T) bytes,
- * 16-byte aligned; one slice for T <= 256 outside the exchange form), then
- * their sum, in slice order, into v.
+ * 16-byte aligned), then their sum, in slice order, into v; one launch where
+ * a batch of T <= 256 takes one slice.
  */
 plora_status plora_shrink(const uint16_t* x, int64_t ldx,
                           const plora_adapters* ad, const plora_segments* seg,

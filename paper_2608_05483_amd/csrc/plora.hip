@@ -10,12 +10,10 @@
 //   plora_shrink   one work group per work item: one tile (up to
 //   plora_expand   PLORA_TILE_TOKENS tokens of one adapter, section VI-B's
 //   plora_apply    per-adapter batch B_i split into tiles) and one slice of
-//                  h_in or of the y columns; plora_apply is one launch for
-//                  batches of up to kFusedTokens tokens (with the tile's
-//                  slices exchanging partial v through the workspace when
-//                  the batch has few tiles) and two above; details above the
-//                  apply kernels below.
-#include "plora_dev.h"
+//                  h_in or of the y columns: the kernels of plora_small.h for
+//                  batches of up to kFusedTokens tokens, those of plora_dev.h
+//                  above.
+#include "plora_small.h"
 
 #include <mutex>
 
@@ -54,11 +52,10 @@ int cu_count() {
 }
 
 // Apply work groups that one compute unit holds at once, as its LDS allows:
-// the dynamic section for this h_in and max_rank plus the largest static one
-// (segment_apply_kernel's), with slack for the allocation granularity; at
-// most kWGPerCU.  At max_rank 128 (82 KB dynamic) that is one.
+// the dynamic section for this h_in and max_rank with slack for the
+// allocation granularity; at most kWGPerCU.  At max_rank 128 (82 KB dynamic) that is one.
 int wg_per_cu(int32_t h_in, int32_t max_rank) {
-  const size_t per = smem_bytes(h_in, max_rank) + sizeof(LocalTile) + sizeof(ItemStash) + 1024;
+  const size_t per = smem_bytes(h_in, max_rank) + 1024;
   return std::max(1, std::min<int>(kWGPerCU, (int)(kMaxLds / per)));
 }
 
@@ -71,7 +68,6 @@ int slots_for_device(int32_t h_in, int32_t max_rank) {
 // count up to tile_cap with at most s_max slices per tile (see there).
 unsigned grid_for(const ApplyArgs& g, int s_max) {
   const int64_t cap8 = (g.tile_cap + 7) & ~7;
-  if (g.fixed_slices > 0) return (unsigned)std::max<int64_t>(8, cap8 * g.fixed_slices);
   if (s_max <= 1) return (unsigned)std::max<int64_t>(8, cap8);
   // fit = round(kPlanItems slots / n8) >= 2 needs n8 <= 2/3 kPlanItems slots,
   // so n8 fit <= 4/3 kPlanItems slots
@@ -85,29 +81,14 @@ int ks_max_for(int h_in) { return std::max(1, std::min(8, h_in / 512)); }
 // plora_apply runs as one launch for batches of up to kFusedTokens tokens.
 bool fused_for(int32_t T) { return T <= kFusedTokens; }
 
-// Slices per tile of the one-launch form: the resident work groups (target,
-// from slots_for_device, so that every item of the launch is resident at
-// once and no exchange partner waits to be dispatched) over the most tiles
-// the batch can produce (rounded up to 8), to nearest, within
-// [1, min(ks_max, js_max)]; 1 when the tile slots outnumber the exchange
-// regions.  The workspace size does not depend on it.  plora_shrink and
-// plora_expand take the same slices for such batches, so their results carry
-// the very bits of the one-launch apply.
-// (For n projections in one launch, plora_apply_multi, the tile slots of
-// all of them count: n cap8 of them, and the limit is the smallest
-// projection's.)
-int fused_slices_for(int slots8, int lim, int target) {
-  if (slots8 <= 0 || slots8 > kXSlots) return 1;
-  return std::max(1, std::min(lim, (target + slots8 / 2) / slots8));
-}
+// The small-batch kernels stage a slice's x in LDS: up to 8192 rows of h_in
+// in each of at most 8 exchanging slices.
+bool small_for(int32_t T, int32_t h_in) { return fused_for(T) && h_in <= 65536; }
 
+// Most slices of a tile (h_in and the columns alike): slices of at least 512
+// rows and columns, at most 8.
 int slice_limit(int32_t h_in, int32_t h_out) {
   return std::min(ks_max_for(h_in), std::max(1, h_out / kMinSlice));
-}
-
-int fused_slices(int32_t tile_cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
-  return fused_slices_for((tile_cap + 7) & ~7, slice_limit(h_in, h_out),
-                          slots_for_device(h_in, max_rank));
 }
 
 // Workspace sections, each 256-byte aligned: the epochs of the exchange's
@@ -245,14 +226,8 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
   g.max_rank = ad->max_rank; g.tile_cap = seg->tile_cap;
   g.js_max = std::max(1, ad->h_out / kMinSlice);
   g.slots = slots_for_device(ad->h_in, ad->max_rank);
-  // one-launch batches take either S > 1 fixed slices per tile (exchange
-  // form) or one h_in slice and device-chosen column slices; the split calls
-  // take the same slices, so that they reproduce the apply's bits
-  const int fs =
-      fused_for(seg->T) ? fused_slices(seg->tile_cap, ad->h_in, ad->h_out, ad->max_rank) : 0;
-  g.fixed_slices = fs > 1 ? fs : 0;
   g.polls = g_exchange_polls.load();
-  g.ks_max = fs == 1 ? 1 : ks_max_for(ad->h_in);
+  g.ks_max = fused_for(seg->T) ? 1 : ks_max_for(ad->h_in);
   g.count_skips = 1;
   if (needs_ws && seg->T > 0) {
     const WsLayout l = ws_layout(seg->T, ad);
@@ -273,15 +248,50 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
   return PLORA_OK;
 }
 
+// How a small batch's launch is split, from its tile slots (all projections'
+// of them): every slot in S slices that exchange partial v, as many as give
+// kSmallTarget work groups of kST threads, three of which a compute unit
+// holds (7B-shaped decode steps of 64 tokens at rank 16: 121 us for 768, 130
+// for 640, 148 for 1024).  A slice of at least kDeepBytes of A_i streams
+// longer than its chain of latencies: its kernels keep twice the chunks in
+// flight, two work groups per compute unit, and it is better not split
+// further (256 tokens at rank 64: 182 us per step, 192 split in three).  With
+// one slice (small h, or more slots than exchange regions) a work group has a
+// tile to itself.  The kernels stage a slice's x in LDS, so h_in above kSXW
+// sets the fewest slices.
+constexpr int kSmallTarget = 768, kDeepTarget = 512;
+constexpr int64_t kDeepBytes = 128 * 1024;
+
+struct SmallPlan {
+  int S, J;        // h_in slices, column slices (as many)
+  int gl, slots;   // slots per group of the numbering (log2), slots of the launch
+  int deep;
+};
+
+SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
+  SmallPlan p;
+  p.gl = cap <= 1 ? 0 : cap <= 2 ? 1 : cap <= 4 ? 2 : 3;
+  p.slots = (cap + (1 << p.gl) - 1) >> p.gl << p.gl;
+  const int s_min = (h_in + kSXW - 1) / kSXW;
+  auto slices = [&](int target) {
+    if (p.slots > kXSlots && s_min <= 1) return 1;
+    return std::max(s_min, std::min(slice_limit(h_in, h_out), (target + p.slots / 2) / p.slots));
+  };
+  p.S = std::max(1, slices(kSmallTarget));
+  p.deep = (int64_t)h_in * max_rank * 2 / p.S > kDeepBytes;
+  if (p.deep) p.S = std::max(1, slices(kDeepTarget));
+  p.J = p.S;
+  return p;
+}
+
 // plora_segment_apply runs as one launch for batches of up to kSegApplyMax
-// tokens in the exchange form (words (key << tbits) | t with key <= N + 1
+// tokens whose tiles can be split (words (key << tbits) | t with key <= N + 1
 // and tbits 6 up to 64 tokens, 8 above; tokens without an adapter read
 // adapter 0's metadata, so N >= 1).
 bool segment_apply_one_launch(int32_t T, const plora_adapters* ad) {
   const int32_t n_limit = T <= 64 ? (1 << 26) - 1 : (1 << 24) - 1;
-  return T <= kSegApplyMax && ad->n_adapters > 0 && ad->n_adapters < n_limit &&
-         fused_slices(plora_tile_capacity(T, ad->n_adapters), ad->h_in, ad->h_out,
-                      ad->max_rank) > 1;
+  return T <= kSegApplyMax && small_for(T, ad->h_in) && ad->n_adapters > 0 && ad->n_adapters < n_limit &&
+         slice_limit(ad->h_in, ad->h_out) > 1;
 }
 
 typedef void (*ItemLauncher)(const ApplyArgs&, unsigned, size_t, hipStream_t);
@@ -419,6 +429,12 @@ plora_status plora_shrink(const uint16_t* x, int64_t ldx, const plora_adapters* 
   if (ldx < ad->h_in || ldv < ad->max_rank) return PLORA_ERR_INVALID_ARG;
   if ((ldx & 7) || (ldv & 3) || !aligned16(x) || !aligned16(v)) return PLORA_ERR_UNSUPPORTED;
   g.x = x; g.ldx = ldx; g.v = v; g.ldv = ldv;
+  if (small_for(seg->T, g.h_in)) {
+    const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
+    clear_stale_error();
+    launch_small_shrink(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.S), stream);
+    return launch_status();
+  }
   st = launch_items(launch_shrink_part, g, g.ks_max, stream);
   if (st != PLORA_OK) return st;
   clear_stale_error();
@@ -437,6 +453,12 @@ plora_status plora_expand(const float* v, int64_t ldv, const plora_adapters* ad,
   if (ldy < ad->h_out || ldv < ad->max_rank) return PLORA_ERR_INVALID_ARG;
   if ((ldy & 7) || (ldv & 3) || !aligned16(y) || !aligned16(v)) return PLORA_ERR_UNSUPPORTED;
   g.v = const_cast<float*>(v); g.ldv = ldv; g.y = y; g.ldy = ldy;
+  if (small_for(seg->T, g.h_in)) {
+    const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
+    clear_stale_error();
+    launch_small_expand(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.J), stream);
+    return launch_status();
+  }
   return launch_items(launch_expand_v, g, g.js_max, stream);
 }
 
@@ -451,9 +473,13 @@ plora_status plora_apply(const uint16_t* x, int64_t ldx, const plora_adapters* a
   if (ldx < ad->h_in || ldy < ad->h_out) return PLORA_ERR_INVALID_ARG;
   if ((ldx & 7) || (ldy & 7) || !aligned16(x) || !aligned16(y)) return PLORA_ERR_UNSUPPORTED;
   g.x = x; g.ldx = ldx; g.y = y; g.ldy = ldy;
-  if (g.fixed_slices > 1) return launch_items(launch_apply, g, g.js_max, stream);
-  if (fused_for(seg->T))
-    return launch_items(launch_apply_cols, g, g.js_max, stream);
+  if (small_for(seg->T, g.h_in)) {
+    const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
+    clear_stale_error();
+    launch_small_apply(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.J), stream);
+    return launch_status();
+  }
+  if (fused_for(seg->T)) return launch_items(launch_apply_cols, g, g.js_max, stream);
   if (g.tile_cap <= kReadyTiles) {
     clear_stale_error();
     launch_parts(g, grid_for(g, g.ks_max), grid_for(g, g.js_max),
@@ -519,8 +545,10 @@ plora_status plora_segment_apply(const int32_t* idx, const uint16_t* x, int64_t 
   g.x = x; g.ldx = ldx; g.y = y; g.ldy = ldy;
   const SegOut so{seg->perm, seg->seg_ptr, seg->seg_id, seg->meta,
                   reinterpret_cast<int4*>(seg->tiles), seg->cap, seg->tile_cap};
+  const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
   clear_stale_error();
-  launch_segment_apply(g, idx, so, grid_for(g, g.js_max), smem_bytes(g.h_in, g.max_rank), stream);
+  launch_small_segment_apply(SmallArgs{g, p.S, p.J, p.gl, p.deep}, idx, so, (unsigned)(p.slots * p.J + (T <= kDecodeTokens && !p.deep ? 1 : 0)),
+                             stream);
   return launch_status();
 }
 
@@ -546,11 +574,10 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
   if (seg->T == 0) return PLORA_OK;
   if (!x || ldx < ads[0].h_in) return PLORA_ERR_INVALID_ARG;
   if ((ldx & 7) || !aligned16(x)) return PLORA_ERR_UNSUPPORTED;
-  int lim = PLORA_MAX_RANK, max_rank = 0;
+  int max_rank = 0;
   for (int p = 0; p < n_proj; ++p) {
     if (!ys[p] || ldys[p] < ads[p].h_out) return PLORA_ERR_INVALID_ARG;
     if ((ldys[p] & 7) || !aligned16(ys[p])) return PLORA_ERR_UNSUPPORTED;
-    lim = std::min(lim, slice_limit(ads[p].h_in, ads[p].h_out));
     max_rank = std::max(max_rank, ads[p].max_rank);
   }
   if (smem_bytes(ads[0].h_in, max_rank) > kMaxLds) return PLORA_ERR_UNSUPPORTED;
@@ -558,11 +585,11 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
   if (!ws) return PLORA_ERR_INVALID_ARG;
   if (!aligned16(ws)) return PLORA_ERR_UNSUPPORTED;
   if (ws_bytes < l.total) return PLORA_ERR_WORKSPACE_TOO_SMALL;
-  const int cap8 = (seg->tile_cap + 7) & ~7;
-  const int S = fused_for(seg->T)
-                    ? fused_slices_for(n_proj * cap8, lim, slots_for_device(ads[0].h_in, max_rank))
-                    : 1;
-  if (S <= 1) {
+  const int cap = seg->tile_cap <= 8 ? seg->tile_cap : (seg->tile_cap + 7) & ~7;
+  int min_out = ads[0].h_out;
+  for (int p = 1; p < n_proj; ++p) min_out = std::min(min_out, ads[p].h_out);
+  const SmallPlan sp = small_plan(n_proj * cap, ads[0].h_in, min_out, max_rank);
+  if (!small_for(seg->T, ads[0].h_in) || n_proj * cap > kXSlots) {
     // one projection after another (the launch overheads are small next to
     // batches this large)
     for (int p = 0; p < n_proj; ++p) {
@@ -579,9 +606,8 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
   m.g.vpart = reinterpret_cast<float*>(base + l.vpart);
   m.g.x = x;
   m.g.ldx = ldx;
-  m.g.fixed_slices = S;
   m.n_proj = n_proj;
-  m.cap8 = cap8;
+  m.cap = cap;
   for (int p = 0; p < n_proj; ++p) {
     ProjArgs& q = m.proj[p];
     q.A = ads[p].A; q.B = ads[p].B; q.a_len = ads[p].a_len; q.b_len = ads[p].b_len;
@@ -592,7 +618,7 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
     q.max_rank = ads[p].max_rank;
   }
   clear_stale_error();
-  launch_apply_multi(m, (unsigned)(n_proj * cap8 * S), smem_bytes(ads[0].h_in, max_rank), stream);
+  launch_small_multi(m, sp.S, sp.J, sp.gl, sp.deep, (unsigned)(sp.slots * sp.J), stream);
   return launch_status();
 }
 

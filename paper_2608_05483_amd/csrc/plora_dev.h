@@ -10,11 +10,9 @@
 //   plora_shrink   one work group per work item: one tile (up to
 //   plora_expand   PLORA_TILE_TOKENS tokens of one adapter, section VI-B's
 //   plora_apply    per-adapter batch B_i split into tiles) and one slice of
-//                  h_in or of the y columns; plora_apply is one launch for
-//                  batches of up to kFusedTokens tokens (with the tile's
-//                  slices exchanging partial v through the workspace when
-//                  the batch has few tiles) and two above; details above the
-//                  apply kernels below.
+//                  h_in or of the y columns.  Batches of up to kFusedTokens
+//                  tokens run the bodies of plora_small.h, larger ones those
+//                  below.
 //
 // Each kernel lives in a source file of its own (k_*.hip, compiled in
 // parallel), with a host launcher declared at the end of this header;
@@ -134,13 +132,11 @@ __device__ __forceinline__ Rsrc block_rsrc(const uint16_t* p, int64_t n) {
 // Cache policy of adapter reads, set by each kernel's source file before it
 // includes this header: PLORA_ADAPTER_POLICY for the vector paths (tiles of
 // a few tokens), PLORA_MATRIX_POLICY (by default the same) for the matrix
-// and general-rank paths.  The exchange-form kernels read every byte of an
-// adapter's blocks once per call, so they read them non-temporally (2): the
-// caches then keep what is reused, the kernel's code, the token metadata and
-// the exchange words.  The two-part form reads a short segment's adapter
-// (one vector-path tile) once too, but re-reads a long segment's A_i and
-// B_i once per tile (matrix path), from the caches; the two-launch form
-// (shrink and expand launches) keeps the default (0) throughout.
+// and general-rank paths.  The two-part form reads a short segment's adapter
+// (one vector-path tile) once, non-temporally (2), so that the caches keep
+// what is reused; it re-reads a long segment's A_i and B_i once per tile
+// (matrix path), from the caches; the two-launch form (shrink and expand
+// launches) keeps the default (0) throughout.
 #ifndef PLORA_ADAPTER_POLICY
 #define PLORA_ADAPTER_POLICY 0
 #endif
@@ -168,25 +164,20 @@ __device__ __forceinline__ uint4 bld16(Rsrc r, int64_t e, bool ok) {
 // dozen tiles still spreads over the whole chip.  plora_apply takes one of
 // three forms, by batch size:
 //
-//   one launch, S > 1 slices per tile (batches whose tile capacity is at
-//   most 2/3 of the resident work groups: decode batches).  S is chosen on
-//   the host from the tile capacity; item (tile, s) reduces h_in slice s,
-//   trades partial v with the tile's other items through the workspace (see
-//   the exchange below) and expands y column slice s.  Each item reads 1/S
-//   of A_i and of B_i.
+//   up to kFusedTokens tokens: plora_small.h.
 //
-//   one launch, one h_in slice (up to kFusedTokens tokens otherwise): item
-//   (tile, column slice), JS chosen on the device from the tile count that
-//   plora_segment wrote, computes the tile's v over all of h_in, then
-//   expands it with its slice of B_i.  A_i is read by every column slice of
-//   its tile; the slices of a tile are numbered onto one XCD, so the first
-//   read brings A_i into that XCD's L2 and the others hit it.
+//   the same with h_in above 65536: item (tile, column slice), JS chosen on
+//   the device from the tile count that plora_segment wrote, computes the
+//   tile's v over all of h_in, then expands it with its slice of B_i.  A_i
+//   is read by every column slice of its tile; the slices of a tile are
+//   numbered onto one XCD, so the first read brings A_i into that XCD's L2
+//   and the others hit it.
 //
 //   two parts (batches above kFusedTokens tokens): item (tile, h_in slice)
 //   writes its partial v to the workspace; item (tile, column slice) sums
 //   the tile's KS partials in slice order and expands.  Every byte of A_i,
 //   B_i and x is then read by one work group only, and a rank-64 tile's
-//   stream of A_i is split over KS items (the one-launch form above measured
+//   stream of A_i is split over KS items (the column-slice form above measured
 //   79.5 us on the ragged workload of 512 tokens, against 73 for this one as
 //   two launches).  The two parts run as one launch (parts_kernel, the
 //   expand items starting on a tile once its partials are stored), or as a
@@ -234,26 +225,14 @@ constexpr int kNT = 256;             // threads per work group
 constexpr int kW = kNT / 64;         // wavefronts per work group
 constexpr int kWGPerCU = 2;          // resident work groups per compute unit
 // Chunks of A_i and of B_i per thread requested up front by the vector path
-// (the rest follow in batches of kCH).  A decode item needs 4 of each, and a
-// masked slot still costs address cycles ahead of the real ones: the
-// one-launch forms (decode-sized slices) request 4 (decode 14.3 us per
-// launch with 16, 13.6 with 8, 13.15 with 4; the large batch 49.7, 50.1,
-// 49.5), the two-part forms 8 (ragged 62.9 with 16, 62.1 with 8, 62.8 with
-// 4, as two launches; in one launch 60.5 with 8, 60.9 with 4).  A kernel file sets PLORA_PREFETCH_CHUNKS before including this header.
-#ifndef PLORA_PREFETCH_CHUNKS
-#define PLORA_PREFETCH_CHUNKS 8
-#endif
-constexpr int kAP = PLORA_PREFETCH_CHUNKS;
-constexpr int kBP = PLORA_PREFETCH_CHUNKS;
+// (the rest follow in batches of kCH): a masked slot still costs address
+// cycles ahead of the real ones (ragged, two launches: 62.9 us with 16, 62.1
+// with 8, 62.8 with 4; in one launch 60.5 with 8, 60.9 with 4).
+constexpr int kAP = 8;
+constexpr int kBP = 8;
 static_assert(kAP <= kCH || kAP % kCH == 0, "whole batches, or one short one");
 // Columns of x staged in LDS per window by the vector path (and shrink_gen).
-// A decode slice is 512 columns, which a 2048-column window stages without
-// masked slots at one token per tile; a kernel file may set
-// PLORA_X_WINDOW before including this header.
-#ifndef PLORA_X_WINDOW
-#define PLORA_X_WINDOW 4096
-#endif
-constexpr int kXW = PLORA_X_WINDOW;
+constexpr int kXW = 4096;
 constexpr int kChunk = 16384;        // bf16 elements per LDS staging chunk (32 KiB)
 constexpr int kWaveRing = 12288;     // bytes of LDS ring per wavefront (matrix shrink)
 constexpr int kBufElems = kW * kWaveRing / 2 + 16;   // slack for transposed reads past the end
@@ -299,7 +278,6 @@ struct ApplyArgs {
   int32_t ks_max;      // most h_in slices per tile
   int32_t js_max;      // most y column slices per tile
   int32_t slots;       // resident work groups the device holds (item target)
-  int32_t fixed_slices; // > 0: every tile takes exactly this many h_in and y column slices
   int32_t polls;        // polls of a partner's exchange word before computing v alone
   // workspace counters (null without a workspace): [0] work items that
   // computed v alone, [1] tokens skipped for an unusable adapter entry
@@ -341,9 +319,7 @@ __device__ __forceinline__ Plan make_plan(const ApplyArgs& g, SliceKind kind) {
   p.n_tiles = nt < 0 ? 0 : (nt > g.tile_cap ? g.tile_cap : nt);
   const int n8 = (p.n_tiles + 7) & ~7;
   int ks = 1, js = 1;
-  if (g.fixed_slices > 0) {
-    ks = js = g.fixed_slices;
-  } else if (n8 > 0) {
+  if (n8 > 0) {
     const int fit = (kPlanItems * g.slots + n8 / 2) / n8;
     ks = max(1, min(g.ks_max, fit));
     js = max(1, min(g.js_max, fit));
@@ -909,10 +885,10 @@ __device__ __forceinline__ void expand_valu(const ApplyArgs& g, const Tile& t, c
 }
 
 // ---------------------------------------------------------------------------
-// one-launch apply: exchange of a tile's partial v between its slices
+// small batches: exchange of a tile's partial v between its slices
 // ---------------------------------------------------------------------------
 //
-// In the one-launch form every tile is split into S items; item s reduces
+// In the exchange form (plora_small.h) every tile is split into S items; item s reduces
 // rows [s KR, (s+1) KR) of h_in (its partial v) and expands y columns
 // [s W, (s+1) W).  Each item needs the full v, the sum of all S partials.
 // Items publish their partial as 64-bit words {fp32 bits, tag} in a region
@@ -928,7 +904,7 @@ __device__ __forceinline__ void expand_valu(const ApplyArgs& g, const Tile& t, c
 // state is on the device, so the scheme holds under graph replay too.
 // Polling is bounded: if a partner's word has not come after kSpinLimit
 // polls (the partner was never scheduled, say because other work holds the
-// compute units), the item computes v over all of h_in by itself (plain_v):
+// compute units), the item computes v over all of h_in by itself:
 // correct to fp32 accuracy, but summed in another order, so such a call's
 // bits can differ from the usual result.  No item ever waits without bound.
 // The split into slices serves small batches, where a tile's reduction
@@ -944,13 +920,6 @@ constexpr int kSpinLimit = 20000;        // polls of a partner's word before com
 // kFusedTokens tokens) at the largest rank, kMaxSlices words each.
 constexpr int64_t kSlotWords = (int64_t)kMaxSlices * kSmallTile * PLORA_MAX_RANK;
 static_assert((kSmallTile * PLORA_MAX_RANK) % 8 == 0, "the region holds whole groups of 8 entries");
-
-struct Xchg {
-  int s, S, kr;          // this item's slice, the tile's slice count, rows of h_in per slice
-  uint32_t tag;          // this call's tag for the tile slot
-  uint64_t* words;       // the slot's region (see xword)
-  int polls;             // polls before giving up on a partner
-};
 
 __device__ __forceinline__ uint64_t xload(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -992,77 +961,12 @@ __device__ __forceinline__ int64_t xword(int o, int q) {
   return (int64_t)(o >> 3) * (8 * kMaxSlices) + q * 8 + (o & 7);
 }
 
-// Publish this item's partial v (sm.vs) and replace sm.vs by the sum of all
-// S partials, in slice order (the order plora_shrink and the two-part form
-// sum them in).  A word carrying this call's tag never changes again during
-// the call, so a poll simply reloads the entry's S live words (the launch's
-// S slices; the words past them are never read).  Returns false, for the
-// whole work group, if some partner's word did not arrive in time; sm.vs is
-// then undefined.
-__device__ __forceinline__ bool exchange_v(const Tile& t, const Smem& sm, const Xchg& xc) {
-  const int n = t.L * t.r;
-  const uint64_t tagw = (uint64_t)xc.tag << 32;
-  for (int o = threadIdx.x; o < n; o += kNT) {
-    const int l = o / t.r, c = o - l * t.r;
-    xpublish(xc.words + xword(o, xc.s), tagw | __float_as_uint(sm.vs[c * kTT + l]));
-  }
-  bool late = false;
-  for (int o = threadIdx.x; o < n; o += kNT) {
-    const uint64_t* e = xc.words + xword(o, 0);
-    uint64_t w[kMaxSlices];
-    bool ready = false;
-    for (int it = 0; !ready && it <= xc.polls; ++it) {
-      // the partners publish at about the time this item does: a first poll
-      // right away mostly misses and costs a line read (decode: 1.0 KiB per
-      // item and poll); after 1024 cycles it reads 0.2 MB less per launch
-      if (it > 0) __builtin_amdgcn_s_sleep(2);
-      else __builtin_amdgcn_s_sleep(16);
-#pragma unroll
-      for (int q = 0; q < kMaxSlices; ++q) w[q] = q < xc.S ? xpoll(e + q * 8) : 0;
-      ready = true;
-#pragma unroll
-      for (int q = 0; q < kMaxSlices; ++q)
-        ready &= q >= xc.S || (uint32_t)(w[q] >> 32) == xc.tag;
-    }
-    late |= !ready;
-    float v = __uint_as_float((uint32_t)w[0]);
-#pragma unroll
-    for (int q = 1; q < kMaxSlices; ++q)
-      if (q < xc.S) v += __uint_as_float((uint32_t)w[q]);
-    const int l = o / t.r, c = o - l * t.r;
-    sm.vs[c * kTT + l] = v;
-  }
-  return __syncthreads_or(late) == 0;
-}
-
 // A tile's pass: shrink (v of rows [k0, k1) into sm.vs), expand (columns
 // [j0, j1) from sm.vs), or both; with both, the expand's first loads of
-// B_i and y are requested with the shrink's.  The hook runs between the
-// two (the one-launch form's exchange, which turns the partial v into the
-// full one) while those loads travel; only a pass with both takes one.
-struct NoHook {
-  __device__ void operator()() const {}
-};
-
-// Shrink of ranks of 32 and more.  An item's slice of A_i is then long
-// enough that B_i and y requested with it delay it, so where a hook follows
-// (the exchange) they are requested once the shrink is done, to travel
-// during the hook.
-template <int R_OCT, int TG>
-__device__ __forceinline__ void shrink_late(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                            uint4 (&bpre)[bp_depth<TG>()], uint4 (&ypre)[TG],
-                                            bool do_expand, bool hooked) {
-  shrink_valu<R_OCT, TG>(g, t, sm, bpre, ypre, do_expand && !hooked);
-  if (do_expand && hooked) {
-    prefetch_b<bp_depth<TG>()>(g, t, bpre);
-    prefetch_y<TG>(g, t, sm.tok, ypre);
-  }
-}
-
-template <int TG, class H>
+// B_i and y are requested with the shrink's.
+template <int TG>
 __device__ __forceinline__ void valu_tile_tg(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                             bool do_shrink, bool do_expand, bool hooked,
-                                             H&& hook) {
+                                             bool do_shrink, bool do_expand) {
   uint4 bpre[bp_depth<TG>()], ypre[TG];
 #pragma unroll
   for (int i = 0; i < TG; ++i) ypre[i] = make_uint4(0, 0, 0, 0);
@@ -1071,23 +975,21 @@ __device__ __forceinline__ void valu_tile_tg(const ApplyArgs& g, const Tile& t, 
     switch (rank_class(t.r)) {
       case 8: shrink_valu<1, TG>(g, t, sm, bpre, ypre, do_expand); break;
       case 16: shrink_valu<2, TG>(g, t, sm, bpre, ypre, do_expand); break;
-      case 32: shrink_late<4, TG>(g, t, sm, bpre, ypre, do_expand, hooked); break;
-      case 64: shrink_late<8, TG>(g, t, sm, bpre, ypre, do_expand, hooked); break;
-      default: shrink_late<16, TG>(g, t, sm, bpre, ypre, do_expand, hooked); break;
+      case 32: shrink_valu<4, TG>(g, t, sm, bpre, ypre, do_expand); break;
+      case 64: shrink_valu<8, TG>(g, t, sm, bpre, ypre, do_expand); break;
+      default: shrink_valu<16, TG>(g, t, sm, bpre, ypre, do_expand); break;
     }
-    if (hooked) hook();
   } else {
     prefetch_b<bp_depth<TG>()>(g, t, bpre);
   }
   if (do_expand) expand_valu<TG>(g, t, sm, bpre, ypre, have_y);
 }
 
-template <class H>
 __device__ __forceinline__ void valu_tile(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                          bool do_shrink, bool do_expand, bool hooked, H&& hook) {
-  if (t.L == 1) valu_tile_tg<1>(g, t, sm, do_shrink, do_expand, hooked, hook);
-  else if (t.L == 2) valu_tile_tg<2>(g, t, sm, do_shrink, do_expand, hooked, hook);
-  else valu_tile_tg<4>(g, t, sm, do_shrink, do_expand, hooked, hook);
+                                          bool do_shrink, bool do_expand) {
+  if (t.L == 1) valu_tile_tg<1>(g, t, sm, do_shrink, do_expand);
+  else if (t.L == 2) valu_tile_tg<2>(g, t, sm, do_shrink, do_expand);
+  else valu_tile_tg<4>(g, t, sm, do_shrink, do_expand);
 }
 
 // ---------------------------------------------------------------------------
@@ -1416,17 +1318,6 @@ __device__ __forceinline__ void expand_load_y(const ApplyArgs& g, const Tile& t,
   }
 }
 
-// The first chunk's B_i units and y words, requested ahead of the expand.
-template <int MT>
-__device__ __forceinline__ void expand_prefetch(const ApplyArgs& g, const Tile& t,
-                                                const Smem& sm, ExpandPre<MT>& pre) {
-  int toks[MT];
-  expand_toks<MT>(t, sm, toks);
-  const int JC = expand_chunk_cols(t);
-  expand_load_b<MT>(g, t, t.j0, JC, pre);
-  expand_load_y<MT>(g, t, t.j0, JC, toks, pre);
-}
-
 // Output words of this wave's first NJ j tiles of a staged chunk (j tile
 // w + i kW for i < NJ): D^T[j][token] = sum_c B_i[c][j] v[token][c] over the
 // K extent rk, v as its bf16 high and low halves, then y = bf16(y + s D).
@@ -1484,12 +1375,10 @@ __device__ __forceinline__ void expand_jtiles(const uint16_t* Bs, int S, const u
 }
 
 // Expand of a multi-token tile with MT token tiles of 16: D^T[j][token] =
-// sum_c B_i[c][j] (vhi + vlo)[token][c], then y = bf16(y + s D).  Unless
-// `fetched` (expand_prefetch already requested them), the first chunk's
-// B_i and y are requested here, before the hook runs.
-template <int MT, class H>
-__device__ __forceinline__ void expand_mfma(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                            H&& hook, ExpandPre<MT>& pre, bool fetched) {
+// sum_c B_i[c][j] (vhi + vlo)[token][c], then y = bf16(y + s D).
+template <int MT>
+__device__ __forceinline__ void expand_mfma(const ApplyArgs& g, const Tile& t, const Smem& sm) {
+  ExpandPre<MT> pre;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, grp = lane >> 4;
   const int r = t.r;
   const int RK = rk_max(g.max_rank);
@@ -1522,11 +1411,8 @@ __device__ __forceinline__ void expand_mfma(const ApplyArgs& g, const Tile& t, c
       *reinterpret_cast<uint4*>(Bs + r * S + q * 8) = make_uint4(0, 0, 0, 0);
   };
 
-  if (!fetched) {
-    expand_load_b<MT>(g, t, t.j0, JC, pre);
-    expand_load_y<MT>(g, t, t.j0, JC, toks, pre);
-  }
-  hook();
+  expand_load_b<MT>(g, t, t.j0, JC, pre);
+  expand_load_y<MT>(g, t, t.j0, JC, toks, pre);
   for (int ch = 0; ch < nchunks; ++ch) {
     const int j0 = t.j0 + ch * JC;
     const int cols = min(JC, t.j1 - j0);
@@ -1581,18 +1467,10 @@ __device__ __forceinline__ void shrink_mfma_r(const ApplyArgs& g, const Tile& t,
   }
 }
 
-template <int MT, class H>
+template <int MT>
 __device__ __forceinline__ void mfma_tile_mt(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                             bool do_shrink, bool do_expand, bool hooked,
-                                             H&& hook) {
+                                             bool do_shrink, bool do_expand) {
   const int RK = rk_max(g.max_rank);
-  ExpandPre<MT> pre;
-  // with both halves and the hook between them (the exchange form, whose
-  // items read small slices), the expand's first B_i and y loads leave
-  // ahead of the shrink's, so they travel while it runs (tiles of up to 16
-  // tokens: with two token tiles the registers they take would spill)
-  const bool early = MT == 1 && do_shrink && do_expand && hooked;
-  if (early) expand_prefetch<MT>(g, t, sm, pre);
   // v's bf16 split is read for every token row < 16 * MT and column < K extent
   for (int o = threadIdx.x; o < 2 * kTT * RK; o += kNT) sm.vhl[o] = 0;
   lds_sync();
@@ -1602,22 +1480,13 @@ __device__ __forceinline__ void mfma_tile_mt(const ApplyArgs& g, const Tile& t, 
     split_v(t, sm, RK);
     lds_sync();
   }
-  // with a hook, v is final only after it has run: split it again then
-  auto after_b = [&] {
-    if (hooked) {
-      hook();
-      split_v(t, sm, RK);
-      lds_sync();
-    }
-  };
-  if (do_expand) expand_mfma<MT>(g, t, sm, after_b, pre, early);
+  if (do_expand) expand_mfma<MT>(g, t, sm);
 }
 
-template <class H>
 __device__ __forceinline__ void mfma_tile(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                          bool do_shrink, bool do_expand, bool hooked, H&& hook) {
-  if (t.L > 16) mfma_tile_mt<2>(g, t, sm, do_shrink, do_expand, hooked, hook);
-  else mfma_tile_mt<1>(g, t, sm, do_shrink, do_expand, hooked, hook);
+                                          bool do_shrink, bool do_expand) {
+  if (t.L > 16) mfma_tile_mt<2>(g, t, sm, do_shrink, do_expand);
+  else mfma_tile_mt<1>(g, t, sm, do_shrink, do_expand);
 }
 
 // ---------------------------------------------------------------------------
@@ -1728,61 +1597,27 @@ __device__ __forceinline__ void shrink_gen(const ApplyArgs& g, const Tile& t, co
   lds_sync();
 }
 
-// A tile of a rank that is not a multiple of 8: shrink_gen, the hook, then
-// the expand of the vector path (up to 4 tokens) or of the matrix path.
-template <class H>
+// A tile of a rank that is not a multiple of 8: shrink_gen, then the expand
+// of the vector path (up to 4 tokens) or of the matrix path.
 __device__ __forceinline__ void gen_tile(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                         bool do_shrink, bool do_expand, bool hooked, H&& hook) {
+                                         bool do_shrink, bool do_expand) {
   if (do_shrink) {
     if (t.L <= 8) shrink_gen<8>(g, t, sm);
     else if (t.L <= 16) shrink_gen<16>(g, t, sm);
     else shrink_gen<32>(g, t, sm);
-    if (hooked) hook();
   }
   if (do_expand) {
-    if (t.L > 4) mfma_tile(g, t, sm, false, true, false, NoHook{});
-    else valu_tile(g, t, sm, false, true, false, NoHook{});
+    if (t.L > 4) mfma_tile(g, t, sm, false, true);
+    else valu_tile(g, t, sm, false, true);
   }
 }
 
 __device__ __forceinline__ void tile_dispatch(const ApplyArgs& g, const Tile& t,
                                               const Smem& sm, bool do_shrink,
                                               bool do_expand) {
-  if (t.r & 7) gen_tile(g, t, sm, do_shrink, do_expand, false, NoHook{});
-  else if (t.L > vector_tokens(t.r)) mfma_tile(g, t, sm, do_shrink, do_expand, false, NoHook{});
-  else valu_tile(g, t, sm, do_shrink, do_expand, false, NoHook{});
-}
-
-// Shrink of the tile's rows [k0, k1), hook(), then expand of its columns
-// [j0, j1): the expand's first loads of B_i and y are requested with the
-// shrink's, and the hook (the exchange that turns the partial v into the
-// full one) runs while they travel.
-template <class H>
-__device__ __forceinline__ void tile_exchange(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                              H&& hook) {
-  if (t.r & 7) gen_tile(g, t, sm, true, true, true, hook);
-  else if (t.L > vector_tokens(t.r)) mfma_tile(g, t, sm, true, true, true, hook);
-  else valu_tile(g, t, sm, true, true, true, hook);
-}
-
-// tile_exchange for the one-launch forms, whose tiles have at most
-// kSmallTile tokens: only the vector paths (the same ones tile_exchange
-// takes for such tiles), so the matrix-path code and its registers stay out
-// of those kernels.
-template <class H>
-__device__ __forceinline__ void tile_exchange_small(const ApplyArgs& g, const Tile& t,
-                                                    const Smem& sm, H&& hook) {
-  static_assert(kSmallTile <= 2 && kSmallTile <= 4, "the vector paths take these tiles");
-  if (t.r & 7) {
-    shrink_gen<8>(g, t, sm);
-    hook();
-    if (t.L == 1) valu_tile_tg<1>(g, t, sm, false, true, false, NoHook{});
-    else valu_tile_tg<2>(g, t, sm, false, true, false, NoHook{});
-  } else if (t.L == 1) {
-    valu_tile_tg<1>(g, t, sm, true, true, true, hook);
-  } else {
-    valu_tile_tg<2>(g, t, sm, true, true, true, hook);
-  }
+  if (t.r & 7) gen_tile(g, t, sm, do_shrink, do_expand);
+  else if (t.L > vector_tokens(t.r)) mfma_tile(g, t, sm, do_shrink, do_expand);
+  else valu_tile(g, t, sm, do_shrink, do_expand);
 }
 
 // Common prologue: token indices to LDS, v zeroed.
@@ -1794,19 +1629,6 @@ __device__ __forceinline__ Smem tile_prologue(const ApplyArgs& g, int my_tok, vo
   return sm;
 }
 
-// The values the one-launch item carries from phase to phase, parked in LDS
-// and read back (as wave-uniform values) before each phase, so that none of
-// them stays in registers across the inlined shrink and expand bodies.
-struct ItemStash {
-  int a, p0, L, r;
-  float s;
-  int u, slice;
-  int pad;
-  const uint16_t* Ai;
-  const uint16_t* Bi;
-  uint64_t ep;
-};
-
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 __device__ __forceinline__ const uint16_t* uni(const uint16_t* p) {
@@ -1816,20 +1638,8 @@ __device__ __forceinline__ const uint16_t* uni(const uint16_t* p) {
   return reinterpret_cast<const uint16_t*>(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ Tile unstash(const ItemStash* st) {
-  Tile t;
-  t.a = uni(st->a);
-  t.p0 = uni(st->p0);
-  t.L = uni(st->L);
-  t.r = uni(st->r);
-  t.s = __int_as_float(uni(__float_as_int(st->s)));
-  t.Ai = uni(st->Ai);
-  t.Bi = uni(st->Bi);
-  return t;
-}
-
-// What the exchange yields, computed by this item alone when a partner's
-// words never came: v[l][c] = sum over all of h_in of x[tok_l][k] A_i[k][c],
+// A tile's v computed by an expand item alone when its shrink items' partials
+// never came: v[l][c] = sum over all of h_in of x[tok_l][k] A_i[k][c],
 // one entry per thread at a time, k ascending, in fp32.  Kept plain and
 // small: it runs only if a partner work group was not scheduled within
 // kSpinLimit polls, and its sum order differs from the slices', so such a
@@ -1849,68 +1659,6 @@ __device__ __forceinline__ void plain_v(const ApplyArgs& g, const Tile& t, const
     sm.vs[c * kTT + l] = v;
   }
   lds_sync();
-}
-
-// One item of the one-launch form with S = g.fixed_slices > 1 slices per
-// tile: slice s of tile u, exchanging through tile slot `slot` (its region
-// and epoch in the workspace): the shrink of h_in rows [s KR, (s+1) KR),
-// the exchange of partial v with the tile's other items, and the expand of
-// y columns [s W, (s+1) W), whose first loads of B_i and y are issued with
-// the shrink's.  If the exchange times out, plain_v computes v here.  ep is
-// the slot's epoch as the caller read it; src(t, my_tok) fills in the tile
-// (adapter, first position, length) and this thread's token, false for a
-// slot without a usable tile.
-template <class Src>
-__device__ __forceinline__ void apply_item(const ApplyArgs& g, int s, int slot, const uint64_t& ep,
-                                           ItemStash& stash, unsigned char* lds, Src&& src) {
-  {
-    Tile t;
-    int my_tok;
-    t.bad = false;
-    if (!src(t, my_tok)) {
-      count_skipped(g, t, s);
-      return;
-    }
-    if (t.L > kSmallTile) {
-      // longer than the exchange region holds: not a tile plora_segment
-      // gives a batch this small; skipped and counted like an unusable entry
-      t.bad = true;
-      count_skipped(g, t, s);
-      return;
-    }
-    if (threadIdx.x == 0) {
-      stash.a = t.a; stash.p0 = t.p0; stash.L = t.L; stash.r = t.r; stash.s = t.s;
-      stash.u = slot; stash.slice = s; stash.Ai = t.Ai; stash.Bi = t.Bi; stash.ep = ep;
-    }
-    (void)tile_prologue(g, my_tok, lds);           // ends with a barrier
-  }
-  const Smem sm = carve(lds, g.max_rank);
-  const int S = g.fixed_slices;
-  const int KR = ((g.h_in + S - 1) / S + 63) & ~63;
-  const int W = ((g.h_out + S - 1) / S + 15) & ~15;
-  {
-    Tile t = unstash(&stash);
-    const int sl = uni(stash.slice);
-    t.k0 = sl * KR;
-    t.k1 = min(g.h_in, t.k0 + KR);
-    t.j0 = sl * W;
-    t.j1 = min(g.h_out, t.j0 + W);
-    const Xchg xc{sl, S, KR, (uint32_t)(stash.ep + 1),
-                  g.xw + (int64_t)uni(stash.u) * kSlotWords, g.polls};
-    tile_exchange_small(g, t, sm, [&] {
-      if (!exchange_v(t, sm, xc)) {
-        bump(g, 0, 1);
-        plain_v(g, t, sm);
-      }
-      // the slot's epoch is raised as soon as the exchange is over (every
-      // partner has read it, or this item gave up), while the expand runs:
-      // raised at the item's end, the atomics (eight per slot, in series
-      // at memory) held up the launch's end (decode 11.81 -> 11.51 us)
-      if (threadIdx.x == 0)
-        __hip_atomic_fetch_max(g.xep + stash.u, stash.ep + 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    });
-  }
 }
 
 // The per-projection part of a multi-projection apply (see plora_apply_multi).
@@ -1934,7 +1682,7 @@ struct MultiArgs {
   ApplyArgs g;            // shared: x, the segments, the workspace, the plan
   ProjArgs proj[PLORA_MAX_PROJECTIONS];
   int32_t n_proj;
-  int32_t cap8;           // tile capacity rounded up to 8
+  int32_t cap;            // tile slots per projection
 };
 
 // ---------------------------------------------------------------------------
@@ -1956,8 +1704,7 @@ struct SegOut {
 constexpr int kSegApplyMax = 256;         // largest batch of the one-launch form
 
 struct LocalTile {
-  int a, p0, L, t0;       // adapter, first position, length, first token
-  uint32_t tmask;         // token bits of a word
+  int a, p0, L;           // adapter, first position, length
   int wcount[2][kNT / 64];             // per wavefront: segment and tile starts
   int wlast[kNT / 64], wfirst[kNT / 64];   // its last and first segment start
   uint32_t words[kSegApplyMax];        // word of token t
@@ -1966,29 +1713,6 @@ struct LocalTile {
   float scale_of[kSegApplyMax];
   int64_t ao_of[kSegApplyMax], bo_of[kSegApplyMax];
 };
-
-// The tile slot's exchange epoch, requested right after the item's first
-// load (the ids, or the tile record) and before that load is waited for:
-// the vector-memory counter retires in order, so an epoch requested first
-// (an agent-scope load, which goes to memory) held up the first load's wait
-// behind it, and one requested after that wait added its trip to the next
-// load's.  The empty asm statements keep the epoch's request between the
-// first load's request and its first use (the second one takes the loaded
-// value as an operand, so nothing that uses it can move above the request).
-__device__ __forceinline__ uint64_t epoch_after(const ApplyArgs& g, int u, int& first) {
-  __asm__ volatile("" ::: "memory");
-  const uint64_t ep = xload(g.xep + u);
-  __asm__ volatile("" : "+v"(first) : : "memory");
-  return ep;
-}
-
-// The adapter-stack arguments that an item's first steps read (tile_blocks),
-// requested at the kernel's entry with the others: requested at their first
-// use, their scalar-cache miss held up that step (decode 12.01 -> 11.85 us).
-__device__ __forceinline__ void request_adapter_args(const ApplyArgs& g) {
-  __asm__ volatile("" ::"s"(g.A), "s"(g.B), "s"(g.a_len), "s"(g.b_len), "s"(g.A_pool),
-                   "s"(g.B_pool));
-}
 
 // The segmentation of a batch of T <= 64 tokens by one wavefront, the same
 // function plora_segment computes, written to so: tokens ordered by
@@ -2057,114 +1781,6 @@ __device__ __forceinline__ void wave_segment(const ApplyArgs& g, const int32_t* 
   if (lane < 8)
     so.meta[lane] = lane == 0 ? n_seg : lane == 1 ? n_valid : lane == 2 ? n_none
                   : lane == 3 ? n_invalid : lane == 4 ? n_tiles : 0;
-}
-
-// The same function for 64 < T <= kSegApplyMax tokens by the whole work
-// group (kNT threads, thread t holds token t, then sorted position t).
-// Words are (key << 8) | t; segment and tile starts are found with each
-// wavefront's ballots and combined across the wavefronts through LDS
-// (counts for the indices, the last and first start for the segment that
-// spans a wavefront boundary).  Every thread of the work group calls it.
-__device__ __forceinline__ void block_segment(const ApplyArgs& g, const int32_t* idx, int u,
-                                              const SegOut& so, bool write, LocalTile& lt,
-                                              uint64_t& ep) {
-  constexpr int NW = kNT / 64;
-  const int T = g.T, N = g.N;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const bool in = tid < T;
-  int id_in = idx[in ? tid : 0];            // (T >= 1: no branch, so no wait here)
-  ep = epoch_after(g, u, id_in);
-  const int id = in ? id_in : 0;
-  const bool valid = in && id >= 0 && id < N;
-  const bool none = in && id == -1;
-  const bool invalid = in && !valid && !none;
-  const int ida = valid ? id : 0;
-  const int m_r = g.ranks[ida];
-  const float m_s = g.scales[ida];
-  const int64_t m_ao = g.a_off[ida], m_bo = g.b_off[ida];
-  const uint32_t key = valid ? (uint32_t)id : (uint32_t)N + (in ? 0u : 1u);
-  const uint32_t w = (key << 8) | (uint32_t)tid;
-  lt.words[tid] = w;
-  if (tid == 0) lt.L = 0;
-  const int n_none = __syncthreads_count(none);
-  const int n_invalid = __syncthreads_count(invalid);
-  int rank = 0;
-#pragma unroll 8
-  for (int q = 0; q < kNT; q += 4) {
-    const uint4 o = *reinterpret_cast<const uint4*>(lt.words + q);
-    rank += (o.x < w) + (o.y < w) + (o.z < w) + (o.w < w);
-  }
-  lt.sorted[rank] = w;
-  lds_sync();
-  const uint32_t sw = lt.sorted[tid];
-  const uint32_t sprev = lt.sorted[tid > 0 ? tid - 1 : 0];
-  const int kp = (int)(sw >> 8), tp = (int)(sw & 255);
-  const int n_valid = T - n_none - n_invalid;
-  const bool vp = tid < n_valid;
-  const bool sflag = vp && (tid == 0 || (int)(sprev >> 8) != kp);
-  const uint64_t bit = uint64_t(1) << lane;
-  const uint64_t below = bit - 1, upto = below | bit;
-  const uint64_t smask = __ballot(sflag);
-  if (lane == 0) {
-    lt.wcount[0][wv] = __popcll(smask);
-    lt.wlast[wv] = smask ? 64 * wv + 63 - __clzll(smask) : -1;
-    lt.wfirst[wv] = smask ? 64 * wv + __ffsll((long long)smask) - 1 : kNT;
-  }
-  lds_sync();
-  int seg_before = 0, n_seg = 0, last_before = -1, first_after = kNT;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) {
-    n_seg += lt.wcount[0][k];
-    if (k < wv) {
-      seg_before += lt.wcount[0][k];
-      last_before = max(last_before, lt.wlast[k]);
-    } else if (k > wv) {
-      first_after = min(first_after, lt.wfirst[k]);
-    }
-  }
-  const int cur = seg_before + __popcll(smask & upto) - 1;   // segment of position tid
-  const int sstart = (smask & upto) ? 64 * wv + 63 - __clzll(smask & upto) : last_before;
-  const uint64_t later = smask & ~upto;
-  int send = later ? 64 * wv + __ffsll((long long)later) - 1 : first_after;
-  send = min(send, n_valid);                                  // segment end
-  const bool tflag = vp && ((tid - sstart) % kSmallTile) == 0;
-  const uint64_t tmask_w = __ballot(tflag);
-  if (lane == 0) lt.wcount[1][wv] = __popcll(tmask_w);
-  lds_sync();
-  int tiles_before = 0, n_tiles_all = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) {
-    n_tiles_all += lt.wcount[1][k];
-    if (k < wv) tiles_before += lt.wcount[1][k];
-  }
-  const int tu = tiles_before + __popcll(tmask_w & below);  // tile starting here
-  const int n_tiles = min(n_tiles_all, so.tile_cap);
-  const int tlen = min(kSmallTile, send - tid);
-  if (write) {
-    if (in) so.perm[tid] = vp ? tp : -1;
-    if (sflag) {
-      so.seg_ptr[cur] = tid;
-      so.seg_id[cur] = kp;
-    }
-    for (int q = n_seg + tid; q <= so.cap; q += kNT) so.seg_ptr[q] = n_valid;
-    for (int q = n_seg + tid; q < so.cap; q += kNT) so.seg_id[q] = -1;
-    if (tflag && tu < so.tile_cap) so.tiles[tu] = make_int4(kp, tid, tlen, cur);
-    for (int q = n_tiles + tid; q < so.tile_cap; q += kNT) so.tiles[q] = make_int4(-1, 0, 0, -1);
-    if (tid < 8)
-      so.meta[tid] = tid == 0 ? n_seg : tid == 1 ? n_valid : tid == 2 ? n_none
-                   : tid == 3 ? n_invalid : tid == 4 ? n_tiles : 0;
-  }
-  lt.rank_of[tid] = m_r;
-  lt.scale_of[tid] = m_s;
-  lt.ao_of[tid] = m_ao;
-  lt.bo_of[tid] = m_bo;
-  if (tflag && tu == u && u < n_tiles) {     // tile u starts here
-    lt.a = kp;
-    lt.p0 = tid;
-    lt.L = tlen;
-    lt.t0 = tp;
-    lt.tmask = 255u;
-  }
 }
 
 // v of tile row l, column c: the sum of the KS partials in slice order.
@@ -2426,13 +2042,9 @@ void launch_shrink_part(const ApplyArgs& g, unsigned grid, size_t lds, hipStream
 void launch_parts(const ApplyArgs& g, unsigned n_shrink, unsigned n_expand, size_t lds,
                   hipStream_t stream);
 void launch_gather_v(const ApplyArgs& g, unsigned grid, hipStream_t stream);
-void launch_apply(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 void launch_apply_cols(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 void launch_expand_parts(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 void launch_expand_v(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
-void launch_segment_apply(const ApplyArgs& g, const int32_t* idx, const SegOut& so,
-                          unsigned grid, size_t lds, hipStream_t stream);
-void launch_apply_multi(const MultiArgs& m, unsigned grid, size_t lds, hipStream_t stream);
 
 }  // namespace plora_impl
 

@@ -253,3 +253,51 @@ def test_overlong_one_launch_tile_is_skipped_and_counted(P):
     assert (y[rest] == y_ref[rest]).all()
     give_ups, n_skipped = run.ws.counters()
     assert give_ups == 0 and n_skipped == L
+
+
+SMALL_EDGES = [
+    # T, h_in, h_out, ranks (dealt over the adapters), N
+    (1, 8, 8, (1, 128), 2),                    # one chunk of A_i; one column octet
+    (1, 4096, 4096, (16,), 3),                 # one slot: slices spread over the XCDs
+    (3, 1032, 520, (3, 8, 13, 127), 4),        # a group of four slots; short last slices
+    (5, 2056, 5128, (5, 24, 100, 128), 5),     # long slices (deep), several column passes
+    (7, 8200, 1024, (4, 40, 128), 6),          # h_in above one LDS window of x
+    (64, 17000, 1096, (6, 64, 2), 9),          # three slices at least
+    (65, 1024, 2048, (12, 20, 8), 30),         # tiles of two tokens, one over
+    (256, 4104, 4104, (7, 64, 96), 40),        # the largest small batch, deep
+]
+
+
+@pytest.mark.parametrize("T,h_in,h_out,ranks,N", SMALL_EDGES)
+def test_small_batch_edges(P, monkeypatch, T, h_in, h_out, ranks, N):
+    """The small-batch kernels at the edges of their slices, windows and tiles,
+    over ranks of every alignment: within the oracle's bars, and the same bits
+    from segment_apply, from apply and from the split calls; apply_multi of
+    two projections within the bars."""
+    monkeypatch.setitem(W.CONFIGS, "edge",
+                        W.ConfigShape(T, N, h_in, h_out, 8, "uniform", scale=(0.5, 1.0, 2.0)))
+    rng = np.random.default_rng(T * h_in)
+    idx = rng.integers(0, N, size=T).astype(np.int32)
+    if T > 3:
+        idx[1] = -1
+        idx[2] = N + 1
+    w = W.make_workload("edge", seed=77, scale="parity", idx=idx, ranks=np.resize(ranks, N))
+    say(f"small edges T={T} h_in={h_in} h_out={h_out} ranks={ranks}")
+    run = Run(P, w).segment()
+    y = run.apply()
+    yref, yout = oracle_y(w)
+    check_y(y, yref, yout, w, strict_l2=True)
+    assert (run.expand(run.shrink()) == y).all()
+    assert (Run(P, w).segment_apply() == y).all()
+    check_counters(run)
+    w2 = W.make_workload("edge", seed=77, scale="parity", idx=idx, ranks=np.resize(ranks, N),
+                         stack_seed=5)
+    ads = [run.ad, P.Adapters.from_workload(w2)]
+    ws = P.Workspace(T, ads)
+    ys = [dev(np.ascontiguousarray(p.y_base).view(np.int16)) for p in (w, w2)]
+    P.apply_multi(dev(np.ascontiguousarray(w.x).view(np.int16)), ads, run.segs, ys, ws)
+    torch.cuda.synchronize()
+    for p, yy in zip((w, w2), ys):
+        pref, pout = oracle_y(p)
+        check_y(bits16(yy), pref, pout, p, strict_l2=True)
+    assert ws.counters() == (0, 0)
