@@ -233,10 +233,8 @@ constexpr int kBP = 8;
 static_assert(kAP <= kCH || kAP % kCH == 0, "whole batches, or one short one");
 // Columns of x staged in LDS per window by the vector path (and shrink_gen).
 constexpr int kXW = 4096;
-constexpr int kChunk = 16384;        // bf16 elements per LDS staging chunk (32 KiB)
 constexpr int kWaveRing = 12288;     // bytes of LDS ring per wavefront (matrix shrink)
 constexpr int kBufElems = kW * kWaveRing / 2 + 16;   // slack for transposed reads past the end
-static_assert(kBufElems >= kChunk, "the LDS buffer also stages B_i chunks and the x window");
 constexpr int kRK = 32;              // MFMA K step
 constexpr int kMinSlice = 512;       // fewest y columns per work item (but h_out)
 // Items per resident work group the device-chosen plans aim at: two, so that
@@ -495,6 +493,10 @@ __device__ __forceinline__ Smem carve(void* base, int max_rank) {
   s.buf = reinterpret_cast<uint16_t*>(p);
   return s;
 }
+
+// n / d for 0 <= n < 2^21, d >= 1, with rd = 1.0f / d (exact: the quotient's
+// distance from an integer exceeds the rounding of the product).
+__device__ __forceinline__ int div_small(int n, float rd) { return (int)(((float)n + 0.5f) * rd); }
 
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 
@@ -1075,7 +1077,7 @@ __device__ __forceinline__ u32x4_t lds_b128(uint32_t a) {
 // after it (n the wavefront's stages), so it is exact, and the ring's tail
 // waits for no loads of its own that nothing uses.
 // Rows of the last K step past the block are zeroed in LDS before use.
-// Writes v to sm.vs (fp32) and its high/low bf16 split to sm.vhl.
+// Writes v to sm.vs (fp32).
 template <int MT, int R>
 __device__ __forceinline__ void shrink_mfma(const ApplyArgs& g, const Tile& t, const Smem& sm) {
   constexpr int NTN = R < 16 ? 1 : R / 16;
@@ -1090,7 +1092,6 @@ __device__ __forceinline__ void shrink_mfma(const ApplyArgs& g, const Tile& t, c
   static_assert(NAI * 1024 == AB && NXI * 1024 == XB, "stages are whole loads");
   static_assert(D * STG <= kWaveRing, "the ring fits");
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, grp = lane >> 4, lp = lane & 15;
-  const int RK = rk_max(g.max_rank);
   const int nst = (t.k1 - t.k0 + SR - 1) / SR;        // stages over the block
   const int my_n = w < nst ? (nst - w + kW - 1) / kW : 0;
   char* ring = reinterpret_cast<char*>(sm.buf) + w * kWaveRing;
@@ -1219,8 +1220,6 @@ __device__ __forceinline__ void shrink_mfma(const ApplyArgs& g, const Tile& t, c
     lds_sync();
   }
   if (w == 0) {
-    uint16_t* vhi = sm.vhl;
-    uint16_t* vlo = sm.vhl + kTT * RK;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -1228,223 +1227,167 @@ __device__ __forceinline__ void shrink_mfma(const ApplyArgs& g, const Tile& t, c
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int tt = mt * 16 + 4 * grp + i, cidx = nt * 16 + lp;
-          if (tt < t.L && cidx < t.r) {
-            const float val = acc[mt][nt][i];
-            const uint32_t hb = to_bf16(val);
-            const float hv = __uint_as_float(hb << 16);
-            sm.vs[cidx * kTT + tt] = val;
-            vhi[tt * RK + cidx] = (uint16_t)hb;
-            vlo[tt * RK + cidx] = (uint16_t)to_bf16(val - hv);
-          }
+          if (tt < t.L && cidx < t.r) sm.vs[cidx * kTT + tt] = acc[mt][nt][i];
         }
   }
   lds_sync();
 }
 
-// v (fp32, already in sm.vs) to its high/low bf16 split in sm.vhl.
+// v (fp32, in sm.vs) to its high/low bf16 split in sm.vhl: every token row
+// below kTT and column below the K extent rk, zero past the tile and the rank.
 __device__ __forceinline__ void split_v(const Tile& t, const Smem& sm, int RK) {
-  for (int o = threadIdx.x; o < t.L * t.r; o += kNT) {
-    const int tt = o / t.r, c = o - tt * t.r;
-    const float val = sm.vs[c * kTT + tt];
-    const uint32_t hb = to_bf16(val);
-    sm.vhl[tt * RK + c] = (uint16_t)hb;
-    sm.vhl[kTT * RK + tt * RK + c] = (uint16_t)to_bf16(val - __uint_as_float(hb << 16));
-  }
-}
-
-// The matrix-path expand streams B_i in column chunks of JC columns (as
-// many as fit kChunk elements at K extent rk = rk_of(r)), with each
-// wavefront's y words of a chunk in registers.  ExpandPre holds this
-// thread's share of one chunk: its B_i units (before they go to LDS) and
-// the y words of its j tiles.
-constexpr int kJT = 8;                             // j tiles per wave per chunk (max)
-
-template <int MT>
-struct ExpandPre {
-  uint4 breg[8];
-  uint2 yv[kJT][MT];
-};
-
-__device__ __forceinline__ int expand_chunk_cols(const Tile& t) {
-  // whole j tiles of 16 columns, so that a staged chunk (rk rows of the
-  // padded width) stays within kChunk elements
-  return min((kChunk / rk_of(t.r)) & ~15, (t.j1 - t.j0 + 15) / 16 * 16);
-}
-
-// Token of this lane's tile row in token tile nt (-1 past the tile).
-template <int MT>
-__device__ __forceinline__ void expand_toks(const Tile& t, const Smem& sm, int (&toks)[MT]) {
-  const int lane = threadIdx.x & 63;
+  const int tt = threadIdx.x & (kTT - 1);
+  for (int c = 2 * ((int)threadIdx.x / kTT); c < rk_of(t.r); c += 2 * (kNT / kTT)) {
+    uint32_t hi = 0, lo = 0;
 #pragma unroll
-  for (int nt = 0; nt < MT; ++nt) {
-    const int ti = nt * 16 + (lane & 15);
-    toks[nt] = ti < t.L ? sm.tok[ti] : -1;
-  }
-}
-
-// This thread's B_i units of the chunk starting at column j0.
-template <int MT>
-__device__ __forceinline__ void expand_load_b(const ApplyArgs& g, const Tile& t, int j0, int JC,
-                                              ExpandPre<MT>& pre) {
-  const int cols = min(JC, t.j1 - j0);
-  const int per_row = cols >> 3;
-  const int n16 = t.r * per_row;
-  const Rsrc rb = block_rsrc(t.Bi, (int64_t)g.h_out * t.r);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int q = (int)threadIdx.x + j * kNT;
-    const int c = q / per_row, col = q - c * per_row;
-    pre.breg[j] = bld16<kMatrixPolicy>(rb, (int64_t)c * g.h_out + j0 + col * 8, q < n16);
-  }
-}
-
-// y words of this wave's j tiles of the chunk starting at column j0.
-template <int MT>
-__device__ __forceinline__ void expand_load_y(const ApplyArgs& g, const Tile& t, int j0, int JC,
-                                              const int (&toks)[MT], ExpandPre<MT>& pre) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, grp = lane >> 4;
-  const int njt = (min(JC, t.j1 - j0) + 15) / 16;
-  // masked lanes read the tile's first token row at the chunk's first column
-  const int tok0 = __builtin_amdgcn_readfirstlane(toks[0]);   // lane 0: tile row 0
-  const uint16_t* y_safe = g.y + (int64_t)max(tok0, 0) * g.ldy + j0;
-#pragma unroll
-  for (int i = 0; i < kJT; ++i) {
-    const int jt = w + i * kW;
-    const int j = j0 + jt * 16 + 4 * grp;
-    const bool jok = jt < njt && j < t.j1;
-#pragma unroll
-    for (int nt = 0; nt < MT; ++nt)
-      pre.yv[i][nt] = ldg8z(g.y + (int64_t)toks[nt] * g.ldy + j, y_safe, jok && toks[nt] >= 0);
-  }
-}
-
-// Output words of this wave's first NJ j tiles of a staged chunk (j tile
-// w + i kW for i < NJ): D^T[j][token] = sum_c B_i[c][j] v[token][c] over the
-// K extent rk, v as its bf16 high and low halves, then y = bf16(y + s D).
-// The body is straight-line: every K step reads v's operands once for all j
-// tiles and issues the transposed B_i reads of all NJ tiles before their
-// MFMAs, so LDS latency is paid once per K step rather than once per j tile.
-// Tiles past the chunk (jt >= njt) read the chunk's last tile and their
-// words are never stored.
-template <int NJ, int MT>
-__device__ __forceinline__ void expand_jtiles(const uint16_t* Bs, int S, const uint16_t* vhi,
-                                              const uint16_t* vlo, int RK, int rk, int w,
-                                              int njt, float s, const ExpandPre<MT>& pre,
-                                              uint2 (&out)[kJT][MT]) {
-  const int lane = threadIdx.x & 63, grp = lane >> 4;
-  f32x4_t acc[NJ][MT];
-#pragma unroll
-  for (int i = 0; i < NJ; ++i)
-#pragma unroll
-    for (int nt = 0; nt < MT; ++nt) acc[i][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int kc = 0; kc < rk; kc += kRK) {
-    uint4 h[MT], lo[MT];
-#pragma unroll
-    for (int nt = 0; nt < MT; ++nt) {
-      const int tt = nt * 16 + (lane & 15);
-      h[nt] = *reinterpret_cast<const uint4*>(vhi + tt * RK + kc + 8 * grp);
-      lo[nt] = *reinterpret_cast<const uint4*>(vlo + tt * RK + kc + 8 * grp);
+    for (int e = 0; e < 2; ++e) {
+      const float val = tt < t.L && c + e < t.r ? sm.vs[(c + e) * kTT + tt] : 0.f;
+      const uint32_t hb = to_bf16(val);
+      hi |= hb << (16 * e);
+      lo |= to_bf16(val - __uint_as_float(hb << 16)) << (16 * e);
     }
-    bf16x8_t a[NJ];
-#pragma unroll
-    for (int i = 0; i < NJ; ++i) a[i] = tr_operand(Bs, S, kc, min(w + i * kW, njt - 1) * 16);
-#pragma unroll
-    for (int i = 0; i < NJ; ++i)
-#pragma unroll
-      for (int nt = 0; nt < MT; ++nt) {
-        acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], as_bf16x8(h[nt]), acc[i][nt], 0, 0, 0);
-        acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], as_bf16x8(lo[nt]), acc[i][nt], 0, 0, 0);
-      }
+    *reinterpret_cast<uint32_t*>(sm.vhl + tt * RK + c) = hi;
+    *reinterpret_cast<uint32_t*>(sm.vhl + kTT * RK + tt * RK + c) = lo;
   }
-#pragma unroll
-  for (int i = 0; i < kJT; ++i)
-#pragma unroll
-    for (int nt = 0; nt < MT; ++nt) {
-      if (i < NJ) {
-        const uint2 yw = pre.yv[i][nt];
-        const float y0 = bf_lo(yw.x), y1 = bf_hi(yw.x), y2 = bf_lo(yw.y), y3 = bf_hi(yw.y);
-        const uint32_t o0 = to_bf16(fmaf(s, acc[i < NJ ? i : 0][nt][0], y0));
-        const uint32_t o1 = to_bf16(fmaf(s, acc[i < NJ ? i : 0][nt][1], y1));
-        const uint32_t o2 = to_bf16(fmaf(s, acc[i < NJ ? i : 0][nt][2], y2));
-        const uint32_t o3 = to_bf16(fmaf(s, acc[i < NJ ? i : 0][nt][3], y3));
-        out[i][nt] = make_uint2(o0 | (o1 << 16), o2 | (o3 << 16));
-      } else {
-        out[i][nt] = make_uint2(0, 0);
-      }
-    }
 }
 
 // Expand of a multi-token tile with MT token tiles of 16: D^T[j][token] =
 // sum_c B_i[c][j] (vhi + vlo)[token][c], then y = bf16(y + s D).
-template <int MT>
-__device__ __forceinline__ void expand_mfma(const ApplyArgs& g, const Tile& t, const Smem& sm) {
-  ExpandPre<MT> pre;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, grp = lane >> 4;
-  const int r = t.r;
-  const int RK = rk_max(g.max_rank);
-  const int rk = rk_of(r);                         // K extent, zero rows from r on
-  const int JC = expand_chunk_cols(t);             // columns per chunk
-  const int nchunks = (t.j1 - t.j0 + JC - 1) / JC;
-  uint16_t* Bs = sm.buf;
+//
+// Each wavefront takes blocks of CW columns by itself (no barrier): its B_i
+// rows go through registers into its own LDS region and come back transposed
+// as the A operand (rows CW + 8 elements apart, so that the transposed reads
+// spread over the banks); D goes back through the same region, which turns the
+// lanes' four columns of one token into whole 16-byte units of a row, so that
+// y is read and written in full lines.  The next block's B_i and y travel
+// while a block is computed.  Bound by y (and, for short tiles, B_i) from HBM.
+// The former form staged one chunk of B_i for the whole work group between
+// barriers and touched y in pieces of 32 bytes: 16384 tokens of 7 segments at
+// h_out = 4096, ranks 16 and 64, XPAND_LONG; 8317 tokens of 32 segments at h_out =
+// 1024, rank 32, XPAND_KV (plora_expand).
+template <int MT, int CW, int NB>
+__device__ __forceinline__ void expand_blocks(const ApplyArgs& g, const Tile& t, const Smem& sm) {
+  constexpr int U = CW / 8;                       // 16-byte units per row
+  constexpr int S = CW + 8;                       // row stride of the staged B_i
+  constexpr int DS = CW + 4;                      // row stride of D, fp32
+  constexpr int NY = MT * 16 * U / 64;            // y units per lane
+  constexpr int NJ = CW / 16;                     // j tiles
+  constexpr int kRegion = kWaveRing / 2;          // elements of a wavefront's region
+  static_assert(NB * 64 / U * S <= kRegion && MT * 16 * DS * 2 <= kRegion, "the region holds both");
+  static_assert(kW * kRegion <= kBufElems, "a region for each wavefront");
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, grp = lane >> 4;
+  const int RK = rk_max(g.max_rank), rk = rk_of(t.r);
+  uint16_t* Bs = sm.buf + w * kRegion;
+  float* Ds = reinterpret_cast<float*>(Bs);
   const uint16_t* vhi = sm.vhl;
   const uint16_t* vlo = sm.vhl + kTT * RK;
-  int toks[MT];
-  expand_toks<MT>(t, sm, toks);
-  auto store_b = [&](int j0) {
-    const int cols = min(JC, t.j1 - j0);
-    const int per_row = cols >> 3;
-    const int n16 = r * per_row;
-    const int S = (cols + 15) / 16 * 16;
+  const Rsrc rb = block_rsrc(t.Bi, (int64_t)g.h_out * t.r);
+  const int oc = lane % U;
+  // this lane's y rows (masked rows read the tile's first)
+  int toks[NY];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int q = tid + j * kNT;
-      if (q < n16) {
-        const int c = q / per_row, col = q - c * per_row;
-        *reinterpret_cast<uint4*>(Bs + c * S + col * 8) = pre.breg[j];
-      }
+  for (int i = 0; i < NY; ++i) {
+    const int row = (lane + 64 * i) / U;
+    toks[i] = row < t.L ? sm.tok[row] : -1;
+  }
+  const uint16_t* y0 = g.y + (int64_t)max(sm.tok[0], 0) * g.ldy;
+  const int nblk = (t.j1 - t.j0 + CW - 1) / CW;
+  uint4 br[NB], yr[NY];
+  auto load_b = [&](int j) {
+    const bool ok = oc * 8 < t.j1 - j;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int row = (lane + 64 * i) / U;
+      br[i] = bld16<kMatrixPolicy>(rb, (int64_t)row * g.h_out + j + oc * 8, ok && row < t.r);
     }
-    // zero padding: columns [cols, S) of rows < r, and rows [r, rk)
-    if (S != cols)
-      for (int c = tid; c < r; c += kNT)
-        *reinterpret_cast<uint4*>(Bs + c * S + cols) = make_uint4(0, 0, 0, 0);
-    for (int q = tid; q < (rk - r) * (S >> 3); q += kNT)
-      *reinterpret_cast<uint4*>(Bs + r * S + q * 8) = make_uint4(0, 0, 0, 0);
   };
-
-  expand_load_b<MT>(g, t, t.j0, JC, pre);
-  expand_load_y<MT>(g, t, t.j0, JC, toks, pre);
-  for (int ch = 0; ch < nchunks; ++ch) {
-    const int j0 = t.j0 + ch * JC;
-    const int cols = min(JC, t.j1 - j0);
-    const int S = (cols + 15) / 16 * 16;
-    const int njt = S / 16;
-    store_b(j0);
-    lds_sync();
-    // the next chunk of B_i (this chunk's y words came before)
-    if (ch + 1 < nchunks) expand_load_b<MT>(g, t, j0 + JC, JC, pre);
-    // every j tile's output words first, then every store: a use of a y
-    // word after a store makes the compiler wait for that store too (the
-    // guards hide the exact count from it), which serialised one store
-    // round trip per j tile
-    uint2 out[kJT][MT];
-    const int nj = (njt - w + kW - 1) / kW;          // this wave's j tiles
-    if (nj > 4) expand_jtiles<8, MT>(Bs, S, vhi, vlo, RK, rk, w, njt, t.s, pre, out);
-    else if (nj > 2) expand_jtiles<4, MT>(Bs, S, vhi, vlo, RK, rk, w, njt, t.s, pre, out);
-    else expand_jtiles<2, MT>(Bs, S, vhi, vlo, RK, rk, w, njt, t.s, pre, out);
-    // this chunk's y words are used: request the next chunk's, which travel
-    // during the stores and the next chunk's staging
-    if (ch + 1 < nchunks) expand_load_y<MT>(g, t, j0 + JC, JC, toks, pre);
+  auto load_y = [&](int j) {
+    const bool ok = oc * 8 < t.j1 - j;
 #pragma unroll
-    for (int i = 0; i < kJT; ++i) {
-      const int jt = w + i * kW;
-      const int j = j0 + jt * 16 + 4 * grp;
+    for (int i = 0; i < NY; ++i)
+      yr[i] = ldg16z(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8, y0 + j, ok && toks[i] >= 0);
+  };
+  if (w < nblk) {
+    load_b(t.j0 + w * CW);
+    load_y(t.j0 + w * CW);
+  }
+#pragma unroll 1
+  for (int b = w; b < nblk; b += kW) {
+    const int j = t.j0 + b * CW;
+    const bool more = b + kW < nblk;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int u = lane + 64 * i;
+      *reinterpret_cast<uint4*>(Bs + u / U * S + oc * 8) = br[i];
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (more) load_b(j + kW * CW);
+    f32x4_t acc[NJ][MT];
+#pragma unroll
+    for (int i = 0; i < NJ; ++i)
+#pragma unroll
+      for (int nt = 0; nt < MT; ++nt) acc[i][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int kc = 0; kc < rk; kc += kRK) {
+      uint4 h[MT], lo[MT];
+#pragma unroll
+      for (int nt = 0; nt < MT; ++nt) {
+        const int tt = nt * 16 + (lane & 15);
+        h[nt] = *reinterpret_cast<const uint4*>(vhi + tt * RK + kc + 8 * grp);
+        lo[nt] = *reinterpret_cast<const uint4*>(vlo + tt * RK + kc + 8 * grp);
+      }
+      bf16x8_t a[NJ];
+#pragma unroll
+      for (int i = 0; i < NJ; ++i) a[i] = tr_operand(Bs, S, kc, i * 16);
+#pragma unroll
+      for (int i = 0; i < NJ; ++i)
+#pragma unroll
+        for (int nt = 0; nt < MT; ++nt) {
+          acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], as_bf16x8(h[nt]), acc[i][nt], 0, 0, 0);
+          acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], as_bf16x8(lo[nt]), acc[i][nt], 0, 0, 0);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    // (LDS operations of one wavefront are processed in order: D replaces the
+    // staged rows once they have been read)
+#pragma unroll
+    for (int i = 0; i < NJ; ++i)
 #pragma unroll
       for (int nt = 0; nt < MT; ++nt)
-        if (jt < njt && toks[nt] >= 0 && j < t.j1)
-          *reinterpret_cast<uint2*>(g.y + (int64_t)toks[nt] * g.ldy + j) = out[i][nt];
+        *reinterpret_cast<f32x4_t*>(Ds + (nt * 16 + (lane & 15)) * DS + i * 16 + 4 * grp) = acc[i][nt];
+    __builtin_amdgcn_wave_barrier();
+    uint4 out[NY];
+#pragma unroll
+    for (int i = 0; i < NY; ++i) {
+      const float* d = Ds + (lane + 64 * i) / U * DS + oc * 8;
+      const f32x4_t d0 = *reinterpret_cast<const f32x4_t*>(d);
+      const f32x4_t d1 = *reinterpret_cast<const f32x4_t*>(d + 4);
+      float yf[8];
+      unpack8(yr[i], yf);
+      uint32_t ob[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ob[e] = to_bf16(fmaf(t.s, d0[e], yf[e]));
+        ob[4 + e] = to_bf16(fmaf(t.s, d1[e], yf[4 + e]));
+      }
+      out[i] = make_uint4(ob[0] | (ob[1] << 16), ob[2] | (ob[3] << 16), ob[4] | (ob[5] << 16),
+                          ob[6] | (ob[7] << 16));
     }
-    lds_sync();
+    __builtin_amdgcn_wave_barrier();
+    // the next block's y leaves ahead of this block's stores
+    if (more) load_y(j + kW * CW);
+#pragma unroll
+    for (int i = 0; i < NY; ++i)
+      if (toks[i] >= 0 && oc * 8 < t.j1 - j)
+        *reinterpret_cast<uint4*>(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8) = out[i];
   }
+}
+
+template <int MT>
+__device__ __forceinline__ void expand_mfma(const ApplyArgs& g, const Tile& t, const Smem& sm) {
+  const int rk = rk_of(t.r);
+  if (rk <= 32) expand_blocks<MT, 64, 4>(g, t, sm);
+  else if (rk <= 64) expand_blocks<MT, 64, 8>(g, t, sm);
+  else expand_blocks<MT, 32, 8>(g, t, sm);
 }
 
 __device__ __forceinline__ void shrink_mfma_r(const ApplyArgs& g, const Tile& t, const Smem& sm) {
@@ -1470,17 +1413,12 @@ __device__ __forceinline__ void shrink_mfma_r(const ApplyArgs& g, const Tile& t,
 template <int MT>
 __device__ __forceinline__ void mfma_tile_mt(const ApplyArgs& g, const Tile& t, const Smem& sm,
                                              bool do_shrink, bool do_expand) {
-  const int RK = rk_max(g.max_rank);
-  // v's bf16 split is read for every token row < 16 * MT and column < K extent
-  for (int o = threadIdx.x; o < 2 * kTT * RK; o += kNT) sm.vhl[o] = 0;
-  lds_sync();
-  if (do_shrink) {
-    shrink_mfma_r(g, t, sm);
-  } else {
-    split_v(t, sm, RK);
+  if (do_shrink) shrink_mfma_r(g, t, sm);
+  if (do_expand) {
+    split_v(t, sm, rk_max(g.max_rank));
     lds_sync();
+    expand_mfma<MT>(g, t, sm);
   }
-  if (do_expand) expand_mfma<MT>(g, t, sm);
 }
 
 __device__ __forceinline__ void mfma_tile(const ApplyArgs& g, const Tile& t, const Smem& sm,
@@ -1834,10 +1772,11 @@ __device__ __forceinline__ void parts_issue(const ApplyArgs& g, int KS, int p0, 
 __device__ __forceinline__ void parts_finish(const ApplyArgs& g, int KS, const Tile& t, int o0,
                                              const PartBatch& pb, const Smem& sm) {
   const int n = t.L * g.max_rank;
+  const float rd = 1.0f / (float)g.max_rank;
 #pragma unroll
   for (int i = 0; i < kSumBatch; ++i) {
     const int o = o0 + i * kNT + threadIdx.x;
-    const int l = o / g.max_rank, c = o - l * g.max_rank;
+    const int l = div_small(o, rd), c = o - l * g.max_rank;
     if (o < n && c < t.r) {
       float v = pb.v[i][0];
 #pragma unroll
@@ -1888,8 +1827,9 @@ __global__ __launch_bounds__(kNT, kWGPerCU) void expand_kernel(ApplyArgs g) {
   }
   const Smem sm = tile_prologue(g, my_tok, apply_lds);
   {
+    const float rd = 1.0f / (float)t.r;
     for (int o = threadIdx.x; o < t.L * t.r; o += kNT) {
-      const int l = o / t.r, c = o - l * t.r;
+      const int l = div_small(o, rd), c = o - l * t.r;
       const int tk = sm.tok[l];
       sm.vs[c * kTT + l] = tk >= 0 ? g.v[(int64_t)tk * g.ldv + c] : 0.f;
     }
@@ -1963,8 +1903,9 @@ __device__ __forceinline__ void parts_shrink_item(const ApplyArgs& g, int i, uns
     const Smem sm = tile_prologue(g, my_tok, lds);
     tile_dispatch(g, t, sm, true, false);
     float* dst = g.vpart + ((int64_t)ks * g.T + t.p0) * g.max_rank;
+    const float rd = 1.0f / (float)t.r;
     for (int o = threadIdx.x; o < t.L * t.r; o += kNT) {
-      const int l = o / t.r, c = o - l * t.r;
+      const int l = div_small(o, rd), c = o - l * t.r;
       __hip_atomic_store(dst + l * g.max_rank + c, sm.vs[c * kTT + l], __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     }
