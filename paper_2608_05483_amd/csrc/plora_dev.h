@@ -106,6 +106,19 @@ __device__ __forceinline__ uint4 ldg16z(const uint16_t* p, const uint16_t* safe,
   return ok ? v : make_uint4(0, 0, 0, 0);
 }
 
+// ldg16z and a 16-byte store with the non-temporal policy, for the y rows of
+// long tiles: each is read and written once per call, and at the default
+// policy the written lines displaced A_i, B_i and x (16384 tokens, h = 4096:
+// 176 -> 148 us per call; 8317 tokens, 8192 -> 1024: 76.7 -> 72.1).
+typedef unsigned int u32x4_nt __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 ldg16nt(const uint16_t* p, const uint16_t* safe, bool ok) {
+  const u32x4_nt v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(ok ? p : safe));
+  return ok ? make_uint4(v.x, v.y, v.z, v.w) : make_uint4(0, 0, 0, 0);
+}
+__device__ __forceinline__ void stg16nt(uint16_t* p, const uint4& v) {
+  __builtin_nontemporal_store(u32x4_nt{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_nt*>(p));
+}
+
 // The 8-byte form of ldg16z.
 __device__ __forceinline__ uint2 ldg8z(const uint16_t* p, const uint16_t* safe, bool ok) {
   const uint2 v = *reinterpret_cast<const uint2*>(ok ? p : safe);
@@ -1262,9 +1275,9 @@ __device__ __forceinline__ void split_v(const Tile& t, const Smem& sm, int RK) {
 // y is read and written in full lines.  The next block's B_i and y travel
 // while a block is computed.  Bound by y (and, for short tiles, B_i) from HBM.
 // The former form staged one chunk of B_i for the whole work group between
-// barriers and touched y in pieces of 32 bytes: 16384 tokens of 7 segments at
-// h_out = 4096, ranks 16 and 64, XPAND_LONG; 8317 tokens of 32 segments at h_out =
-// 1024, rank 32, XPAND_KV (plora_expand).
+// barriers and touched y in pieces of 32 bytes: plora_expand of 16384 tokens
+// of 7 segments at h_out = 4096, ranks 16 and 64, 155 -> 97 us (2.8 TB/s of y);
+// of 8317 tokens of 32 segments at h_out = 1024, rank 32, 34 -> 25.
 template <int MT, int CW, int NB>
 __device__ __forceinline__ void expand_blocks(const ApplyArgs& g, const Tile& t, const Smem& sm) {
   constexpr int U = CW / 8;                       // 16-byte units per row
@@ -1305,7 +1318,7 @@ __device__ __forceinline__ void expand_blocks(const ApplyArgs& g, const Tile& t,
     const bool ok = oc * 8 < t.j1 - j;
 #pragma unroll
     for (int i = 0; i < NY; ++i)
-      yr[i] = ldg16z(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8, y0 + j, ok && toks[i] >= 0);
+      yr[i] = ldg16nt(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8, y0 + j, ok && toks[i] >= 0);
   };
   if (w < nblk) {
     load_b(t.j0 + w * CW);
@@ -1378,7 +1391,7 @@ __device__ __forceinline__ void expand_blocks(const ApplyArgs& g, const Tile& t,
 #pragma unroll
     for (int i = 0; i < NY; ++i)
       if (toks[i] >= 0 && oc * 8 < t.j1 - j)
-        *reinterpret_cast<uint4*>(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8) = out[i];
+        stg16nt(g.y + (int64_t)toks[i] * g.ldy + j + oc * 8, out[i]);
   }
 }
 
