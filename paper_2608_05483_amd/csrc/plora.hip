@@ -256,14 +256,14 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
 // longer than its chain of latencies: its kernels keep twice the chunks in
 // flight, two work groups per compute unit, and it is better not split
 // further (256 tokens at rank 64: 182 us per step, 192 split in three).  With
-// one slice (small h, or more slots than exchange regions) a work group has a
-// tile to itself.  The kernels stage a slice's x in LDS, so h_in above kSXW
+// one slice (small h, or more slots than exchange regions) a work group computes
+// its tile's v whole.  The kernels stage a slice's x in LDS, so h_in above kSXW
 // sets the fewest slices.
 constexpr int kSmallTarget = 768, kDeepTarget = 512;
 constexpr int64_t kDeepBytes = 128 * 1024;
 
 struct SmallPlan {
-  int S, J;        // h_in slices, column slices (as many)
+  int S, J;        // h_in slices, column slices (as many where S > 1)
   int gl, slots;   // slots per group of the numbering (log2), slots of the launch
   int deep;
 };
@@ -280,7 +280,10 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
   p.S = std::max(1, slices(kSmallTarget));
   p.deep = (int64_t)h_in * max_rank * 2 / p.S > kDeepBytes;
   if (p.deep) p.S = std::max(1, slices(kDeepTarget));
-  p.J = p.S;
+  // one slice of h_in: the work groups of a tile's column slices each compute
+  // v whole (h_in is small: 5 tokens, 792 -> 4512, rank 64, 21.5 us undivided)
+  p.J = p.S > 1 || p.slots > kXSlots ? p.S
+        : std::max(1, std::min(h_out / kMinSlice, kSmallTarget / p.slots));
   return p;
 }
 

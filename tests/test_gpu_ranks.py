@@ -261,6 +261,7 @@ SMALL_EDGES = [
     (1, 4096, 4096, (16,), 3),                 # one slot: slices spread over the XCDs
     (3, 1032, 520, (3, 8, 13, 127), 4),        # a group of four slots; short last slices
     (5, 2056, 5128, (5, 24, 100, 128), 5),     # long slices (deep), several column passes
+    (5, 792, 4512, (64, 12, 1), 4),            # one slice of h_in, several of the columns
     (7, 8200, 1024, (4, 40, 128), 6),          # h_in above one LDS window of x
     (64, 17000, 1096, (6, 64, 2), 9),          # three slices at least
     (65, 1024, 2048, (12, 20, 8), 30),         # tiles of two tokens, one over
