@@ -281,7 +281,8 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
   p.deep = (int64_t)h_in * max_rank * 2 / p.S > kDeepBytes;
   if (p.deep) p.S = std::max(1, slices(kDeepTarget));
   // one slice of h_in: the work groups of a tile's column slices each compute
-  // v whole (h_in is small: 5 tokens, 792 -> 4512, rank 64, 21.5 us undivided)
+  // v whole (h_in is small: 5 tokens, 792 -> 4512, rank 64, 12.5 us, 21.5
+  // undivided)
   p.J = p.S > 1 || p.slots > kXSlots ? p.S
         : std::max(1, std::min(h_out / kMinSlice, kSmallTarget / p.slots));
   return p;
