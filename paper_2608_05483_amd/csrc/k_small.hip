@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_shrink_kernel(Sm
     BRegs<small_batch(DEEP)> br;
     YRegs<TG> yr;
     x_issue<TG>(g, t.tok, t.k0, min(t.k1, t.k0 + kSXW), xr);
-    shrink_small<TG, small_batch(DEEP), kReadOnce, false>(g, t, xr, sm, br, yr);
+    shrink_small<TG, small_batch(DEEP), kReadOnce, false, X && DEEP>(g, t, xr, sm, br, yr);
     const int tok0 = t.tok[0], tok1 = t.tok[TG - 1];
     for (int o = threadIdx.x; o < t.r * TG; o += kST) {
       const int c = o / TG, tt = o - c * TG;

@@ -81,10 +81,6 @@ int ks_max_for(int h_in) { return std::max(1, std::min(8, h_in / 512)); }
 // plora_apply runs as one launch for batches of up to kFusedTokens tokens.
 bool fused_for(int32_t T) { return T <= kFusedTokens; }
 
-// The small-batch kernels stage a slice's x in LDS: up to 8192 rows of h_in
-// in each of at most 8 exchanging slices.
-bool small_for(int32_t T, int32_t h_in) { return fused_for(T) && h_in <= 65536; }
-
 // Most slices of a tile (h_in and the columns alike): slices of at least 512
 // rows and columns, at most 8.
 int slice_limit(int32_t h_in, int32_t h_out) {
@@ -227,7 +223,7 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
   g.js_max = std::max(1, ad->h_out / kMinSlice);
   g.slots = slots_for_device(ad->h_in, ad->max_rank);
   g.polls = g_exchange_polls.load();
-  g.ks_max = fused_for(seg->T) ? 1 : ks_max_for(ad->h_in);
+  g.ks_max = ks_max_for(ad->h_in);
   g.count_skips = 1;
   if (needs_ws && seg->T > 0) {
     const WsLayout l = ws_layout(seg->T, ad);
@@ -258,7 +254,8 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
 // further (256 tokens at rank 64: 182 us per step, 192 split in three).  With
 // one slice (small h, or more slots than exchange regions) a work group computes
 // its tile's v whole.  The kernels stage a slice's x in LDS, so h_in above kSXW
-// sets the fewest slices.
+// sets the fewest slices; slices longer than that (h_in above 8 kSXW) are deep,
+// since max_rank is at least 8, and the deep kernels go on window by window.
 constexpr int kSmallTarget = 768, kDeepTarget = 512;
 constexpr int64_t kDeepBytes = 128 * 1024;
 
@@ -272,7 +269,7 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
   SmallPlan p;
   p.gl = cap <= 1 ? 0 : cap <= 2 ? 1 : cap <= 4 ? 2 : 3;
   p.slots = (cap + (1 << p.gl) - 1) >> p.gl << p.gl;
-  const int s_min = (h_in + kSXW - 1) / kSXW;
+  const int s_min = std::min<int>(kMaxSlices, (h_in + kSXW - 1) / kSXW);
   auto slices = [&](int target) {
     if (p.slots > kXSlots && s_min <= 1) return 1;
     return std::max(s_min, std::min(slice_limit(h_in, h_out), (target + p.slots / 2) / p.slots));
@@ -294,7 +291,7 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
 // adapter 0's metadata, so N >= 1).
 bool segment_apply_one_launch(int32_t T, const plora_adapters* ad) {
   const int32_t n_limit = T <= 64 ? (1 << 26) - 1 : (1 << 24) - 1;
-  return T <= kSegApplyMax && small_for(T, ad->h_in) && ad->n_adapters > 0 && ad->n_adapters < n_limit &&
+  return T <= kSegApplyMax && ad->n_adapters > 0 && ad->n_adapters < n_limit &&
          slice_limit(ad->h_in, ad->h_out) > 1;
 }
 
@@ -433,7 +430,7 @@ plora_status plora_shrink(const uint16_t* x, int64_t ldx, const plora_adapters* 
   if (ldx < ad->h_in || ldv < ad->max_rank) return PLORA_ERR_INVALID_ARG;
   if ((ldx & 7) || (ldv & 3) || !aligned16(x) || !aligned16(v)) return PLORA_ERR_UNSUPPORTED;
   g.x = x; g.ldx = ldx; g.v = v; g.ldv = ldv;
-  if (small_for(seg->T, g.h_in)) {
+  if (fused_for(seg->T)) {
     const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
     clear_stale_error();
     launch_small_shrink(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.S), stream);
@@ -457,7 +454,7 @@ plora_status plora_expand(const float* v, int64_t ldv, const plora_adapters* ad,
   if (ldy < ad->h_out || ldv < ad->max_rank) return PLORA_ERR_INVALID_ARG;
   if ((ldy & 7) || (ldv & 3) || !aligned16(y) || !aligned16(v)) return PLORA_ERR_UNSUPPORTED;
   g.v = const_cast<float*>(v); g.ldv = ldv; g.y = y; g.ldy = ldy;
-  if (small_for(seg->T, g.h_in)) {
+  if (fused_for(seg->T)) {
     const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
     clear_stale_error();
     launch_small_expand(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.J), stream);
@@ -477,13 +474,12 @@ plora_status plora_apply(const uint16_t* x, int64_t ldx, const plora_adapters* a
   if (ldx < ad->h_in || ldy < ad->h_out) return PLORA_ERR_INVALID_ARG;
   if ((ldx & 7) || (ldy & 7) || !aligned16(x) || !aligned16(y)) return PLORA_ERR_UNSUPPORTED;
   g.x = x; g.ldx = ldx; g.y = y; g.ldy = ldy;
-  if (small_for(seg->T, g.h_in)) {
+  if (fused_for(seg->T)) {
     const SmallPlan p = small_plan(g.tile_cap, g.h_in, g.h_out, g.max_rank);
     clear_stale_error();
     launch_small_apply(SmallArgs{g, p.S, p.J, p.gl, p.deep}, (unsigned)(p.slots * p.J), stream);
     return launch_status();
   }
-  if (fused_for(seg->T)) return launch_items(launch_apply_cols, g, g.js_max, stream);
   if (g.tile_cap <= kReadyTiles) {
     clear_stale_error();
     launch_parts(g, grid_for(g, g.ks_max), grid_for(g, g.js_max),
@@ -593,7 +589,7 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
   int min_out = ads[0].h_out;
   for (int p = 1; p < n_proj; ++p) min_out = std::min(min_out, ads[p].h_out);
   const SmallPlan sp = small_plan(n_proj * cap, ads[0].h_in, min_out, max_rank);
-  if (!small_for(seg->T, ads[0].h_in) || n_proj * cap > kXSlots) {
+  if (!fused_for(seg->T) || n_proj * cap > kXSlots) {
     // one projection after another (the launch overheads are small next to
     // batches this large)
     for (int p = 0; p < n_proj; ++p) {

@@ -175,24 +175,17 @@ __device__ __forceinline__ uint4 bld16(Rsrc r, int64_t e, bool ok) {
 // rows) or of the y columns (JS slices of W columns), so that each launch
 // has about kPlanItems items per resident work group and a batch of a few
 // dozen tiles still spreads over the whole chip.  plora_apply takes one of
-// three forms, by batch size:
+// two forms, by batch size:
 //
 //   up to kFusedTokens tokens: plora_small.h.
-//
-//   the same with h_in above 65536: item (tile, column slice), JS chosen on
-//   the device from the tile count that plora_segment wrote, computes the
-//   tile's v over all of h_in, then expands it with its slice of B_i.  A_i
-//   is read by every column slice of its tile; the slices of a tile are
-//   numbered onto one XCD, so the first read brings A_i into that XCD's L2
-//   and the others hit it.
 //
 //   two parts (batches above kFusedTokens tokens): item (tile, h_in slice)
 //   writes its partial v to the workspace; item (tile, column slice) sums
 //   the tile's KS partials in slice order and expands.  Every byte of A_i,
 //   B_i and x is then read by one work group only, and a rank-64 tile's
-//   stream of A_i is split over KS items (the column-slice form above measured
-//   79.5 us on the ragged workload of 512 tokens, against 73 for this one as
-//   two launches).  The two parts run as one launch (parts_kernel, the
+//   stream of A_i is split over KS items (column slices that each compute the
+//   tile's v over all of h_in measured 79.5 us on the ragged workload of 512
+//   tokens, against 73 for this form as two launches).  The two parts run as one launch (parts_kernel, the
 //   expand items starting on a tile once its partials are stored), or as a
 //   shrink launch and an expand launch for a batch with more tile slots than
 //   the workspace has readiness words.
@@ -1996,7 +1989,6 @@ void launch_shrink_part(const ApplyArgs& g, unsigned grid, size_t lds, hipStream
 void launch_parts(const ApplyArgs& g, unsigned n_shrink, unsigned n_expand, size_t lds,
                   hipStream_t stream);
 void launch_gather_v(const ApplyArgs& g, unsigned grid, hipStream_t stream);
-void launch_apply_cols(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 void launch_expand_parts(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 void launch_expand_v(const ApplyArgs& g, unsigned grid, size_t lds, hipStream_t stream);
 

@@ -446,11 +446,50 @@ __device__ __forceinline__ float column_sum(float x, int RP) {
 
 // ---- shrink ---------------------------------------------------------------------
 
+// acc += x A_i of rows [w0, w1), window by window: what of a slice lies past
+// its first kSXW rows (h_in above 8 kSXW = 65536, since a tile has at most 8
+// slices).  Such a launch is always a deep one that exchanges, so only those
+// kernels have this loop (it cost the others registers, and one of them a
+// spill).  x goes straight to LDS and one batch of chunks is in flight.
+// (65544 -> 4096 at rank 16, one token 13.3 us, 200 tokens 39; whole-v column
+// slices 71 and 220, the former exchange kernels 17.4 and 46.)
+template <int TG, int SU, int POL>
+__device__ __forceinline__ void shrink_rest(const ApplyArgs& g, const SmallItem<TG>& t, int w0,
+                                            const FlatMap& m, bool aligned, bool active,
+                                            SmallLds<TG>& sm, float (&acc)[TG][8]) {
+  const uint32_t step = (uint32_t)m.nt * 16u;
+#pragma unroll 1
+  for (; w0 < t.k1; w0 += kSXW) {
+    const int rows = min(kSXW, t.k1 - w0);
+    lds_sync();                                     // the window before is read
+#pragma unroll
+    for (int tt = 0; tt < TG; ++tt) {
+      const uint16_t* row = g.x + (int64_t)max(t.tok[tt], 0) * g.ldx;
+#pragma unroll 1
+      for (int c = threadIdx.x; c < rows >> 3; c += kST)
+        *reinterpret_cast<uint4*>(&sm.xs[tt][c * 8]) = ldg16z(row + w0 + c * 8, row, t.tok[tt] >= 0);
+    }
+    lds_sync();
+    const int Q = rows * t.r / 8;
+    const int nj = active && (int)threadIdx.x < Q ? (Q - (int)threadIdx.x + m.nt - 1) / m.nt : 0;
+    const Rsrc ra = block_rsrc(t.Ai + (int64_t)w0 * t.r, (int64_t)rows * t.r);
+    uint32_t vo = active ? (uint32_t)threadIdx.x * 16u : (uint32_t)kPastEnd;
+#pragma unroll 1
+    for (int jb = 0; jb * m.nt < Q; jb += SU) {
+      uint4 a[SU];
+      load_steps<POL>(ra, vo, step, a);
+      vo += active ? SU * step : 0;
+      flat_fma<TG, SU>(acc, a, sm, m, aligned, jb, nj, Q / m.nt);
+    }
+  }
+}
+
 // v of rows [t.k0, t.k1) into sm.vs.  xr holds the first window's x
 // (x_issue).  With EXP, the item's first B_i rows and y words are requested
 // too: with A_i where the thread's chunks fit two batches, else once A_i is
-// read (requested ahead of a longer stream they would hold it up).
-template <int TG, int SU, int POL, bool EXP>
+// read (requested ahead of a longer stream they would hold it up).  MORE: the
+// slice may be longer than one window.
+template <int TG, int SU, int POL, bool EXP, bool MORE>
 __device__ __forceinline__ void shrink_small(const ApplyArgs& g, const SmallItem<TG>& t,
                                              XRegs<TG>& xr, SmallLds<TG>& sm, BRegs<SU>& br,
                                              YRegs<TG>& yr) {
@@ -465,12 +504,12 @@ __device__ __forceinline__ void shrink_small(const ApplyArgs& g, const SmallItem
   for (int tt = 0; tt < TG; ++tt)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[tt][e] = 0.f;
-  const int rows = t.k1 - t.k0;                     // at most kSXW (the host sees to it)
-  const int Q = rows * r / 8;                       // chunks of the slice
+  const int rows = min(kSXW, t.k1 - t.k0);          // the first window
+  const int Q = rows * r / 8;                       // its chunks
   const int njm = (Q + m.nt - 1) / m.nt;
   const int nj = active && tid < Q ? (Q - tid + m.nt - 1) / m.nt : 0;
   const int n_full = Q / m.nt;                      // chunks that all active threads have
-  // the slice's rows as a resource of their own: chunks past it read zero
+  // the window's rows as a resource of their own: chunks past it read zero
   const Rsrc ra = block_rsrc(t.Ai + (int64_t)t.k0 * r, (int64_t)rows * r);
   uint32_t vo = active ? (uint32_t)tid * 16u : (uint32_t)kPastEnd;
   uint4 a0[SU], a1[SU];
@@ -498,6 +537,8 @@ __device__ __forceinline__ void shrink_small(const ApplyArgs& g, const SmallItem
     }
     if (EXP) b_issue<TG, SU>(g, t, br, yr);
   }
+  if constexpr (MORE)
+    shrink_rest<TG, SU, POL>(g, t, t.k0 + kSXW, m, aligned, active, sm, acc);
   lds_sync();                                       // x is dead
   // column c's entries are the flat positions c, c + r, ... of the active
   // threads' accumulators: thread (c, ph) sums every NPH-th of them, the
@@ -762,7 +803,7 @@ __device__ __forceinline__ void small_body(const ApplyArgs& g, const SmallItem<T
   constexpr int SU = small_batch(DEEP);
   BRegs<SU> br;
   YRegs<TG> yr;
-  shrink_small<TG, SU, kReadOnce, !(X && DEEP)>(g, t, xr, sm, br, yr);
+  shrink_small<TG, SU, kReadOnce, !(X && DEEP), X && DEEP>(g, t, xr, sm, br, yr);
   if constexpr (X && DEEP)
     small_exchange<TG>(g, t, sm, s, S, slot, ep, o0, last, [&] { b_issue<TG, SU>(g, t, br, yr); });
   else if constexpr (X)

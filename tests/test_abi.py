@@ -363,6 +363,13 @@ def test_segment_apply_launch_count():
     assert P.plora_segment_apply_launches(8, _ad(h_in=12)) == 0
 
 
+@pytest.mark.parametrize("h_in", [8192, 8200, 65536, 65544, 1 << 20])
+def test_segment_apply_is_one_launch_whatever_h_in(h_in):
+    for T in (1, 64, 65, 256):
+        ad = _ad(n_adapters=1000, h_in=h_in, h_out=4096, max_rank=16)
+        assert P.plora_segment_apply_launches(T, ad) == 1
+
+
 def test_attention_host_checks():
     L = P.lib
     assert P.attn_partitions(0) == 0 and P.attn_partitions(1) == 1

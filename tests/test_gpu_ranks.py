@@ -266,6 +266,11 @@ SMALL_EDGES = [
     (64, 17000, 1096, (6, 64, 2), 9),          # three slices at least
     (65, 1024, 2048, (12, 20, 8), 30),         # tiles of two tokens, one over
     (256, 4104, 4104, (7, 64, 96), 40),        # the largest small batch, deep
+    (9, 8192, 512, (8, 13, 128), 5),           # one slice that fills the LDS window
+    (5, 65536, 256, (8, 13), 3),               # eight full windows, slices without columns
+    (3, 65544, 1032, (8, 13, 100), 3),         # slices of a window and 64 rows
+    (66, 65544, 520, (8, 1), 20),              # the same, tiles of two tokens
+    (2, 131080, 2048, (16, 5), 2),             # slices of three windows
 ]
 
 
