@@ -95,13 +95,13 @@ __device__ __forceinline__ float row_sum(float x) {
 // meet only at the end, where the groups are rescaled to the common anchor.
 // With out set (P = 1) the only partition is the whole cache and is written
 // as the output itself.
-// The partitions of a head start at another one for each head: in grid order
-// partition p of every head would run on XCD p mod P where P divides 8, and
-// the last partitions, past most requests' lengths, would leave their XCDs
-// idle (64 x 32 x 512..4096 keys: 507 us at 512-key partitions, 367 rotated;
-// 434 and 386 at 256).  The former kernel (256-key partitions, all 32 units
-// of a thread requested at once, reductions through LDS, default cache
-// policy) took 446 us there.
+// The XCDs take the work groups in turn, so where P and 8 have a factor g in
+// common a partition number would stay on 8 / g of the XCDs, and the last
+// partitions, past most requests' lengths, would leave theirs idle: the
+// partitions start at the next one after every 8 / g heads (64 x 32 x
+// 512..4096 keys: 507 us at 512-key partitions without, 367 with; 434 and 386
+// at 256).  An odd P spreads by itself: turned by one per head, three
+// partitions (8 x 32 x 260..520 keys) took 15.4 us against 13.9 in grid order.
 // Bound by reading K and V; the loads in flight come from the resident work
 // groups (four per compute unit), so no stage is requested ahead of another.
 __global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
@@ -112,7 +112,9 @@ __global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
   __shared__ float red[kNT / 64][kD];
   __shared__ float wmax[kNT / 64], wsum[kNT / 64];
   const int h = blockIdx.y, b = blockIdx.z;
-  const int p = (int)((blockIdx.x + (uint32_t)b * (uint32_t)heads + (uint32_t)h) % (uint32_t)P);
+  const uint32_t head = (uint32_t)b * (uint32_t)heads + (uint32_t)h;
+  const int lg = min(3, (int)__builtin_ctz(P));
+  const int p = (int)((blockIdx.x + (lg ? head >> (3 - lg) : 0u)) % (uint32_t)P);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int g = tid >> 4, e = tid & 15;
   int n = lens[b];
