@@ -23,10 +23,11 @@ namespace {
 constexpr int kD = PLORA_ATTN_HEAD_DIM;   // 128: sixteen 16-byte units per row
 constexpr int kC = PLORA_ATTN_CHUNK;      // keys per partition of the ABI
 constexpr int kNT = 256;                  // threads per work group
+constexpr int kCUs = 256;                 // compute units of the chip
 constexpr int kGroups = kNT / 16;         // keys per pass (16 lanes each)
 constexpr int kStage = 8;                 // keys per 16-lane group and stage
-constexpr int kStageKeys = kStage * kGroups;   // keys per stage of a work group
-static_assert(kC % kStageKeys == 0, "partitions are whole stages");
+constexpr int kWholeStage = kC / kGroups; // the same where a partition is one stage
+static_assert(kC % (kStage * kGroups) == 0, "partitions are whole stages");
 
 // (the merge takes partials and outputs of any element alignment)
 typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -35,6 +36,7 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2), aligned(2)));
 typedef uint32_t u32x1_t __attribute__((aligned(2)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kRsrcWord3 = 0x00020000;    // raw buffer, 32-bit data format (gfx9 family)
+constexpr int kCached = 0, kOnce = 2;     // buffer cache policies: default, non-temporal
 constexpr int kPastEnd = (int)0x80000000u;
 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -64,10 +66,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint16_t* p, i
                                            kRsrcWord3);
 }
 
-// Non-temporal: every key and value is read once per call (a plain read of
-// 2.4 GB runs at 7.1 TB/s non-temporally, at 6.3 otherwise).
+// POL: the cache policy (see keep_cached).
+template <int POL>
 __device__ __forceinline__ uint4 bld16(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  const i32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 2);
+  const i32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, POL);
   return make_uint4((uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w);
 }
 
@@ -91,12 +93,12 @@ __device__ __forceinline__ float row_sum(float x) {
 // request blockIdx.z.  Thread (g, e) = (tid / 16, tid % 16) takes keys g,
 // g + 16, ... of the partition and the dimensions 8 e .. 8 e + 7 of each: the
 // sixteen lanes of a key read its row as one coalesced 256-byte line.  A
-// stage is eight keys per group (128 keys), all of whose key and value units
-// are requested before any is used; each group keeps its own running maximum,
-// sum and output (rescaled once per stage), so the work group's wavefronts
-// meet only at the end, where the groups are rescaled to the common anchor.
-// With out set (P = 1) the only partition is the whole cache and is written
-// as the output itself.
+// stage is ST keys per group, all of whose key and value units are requested
+// before any is used; each group keeps its own running maximum, sum and output
+// (rescaled once per stage), so the work group's wavefronts meet only at the
+// end, where the groups are rescaled to the common anchor.  With out set
+// (P = 1) the only partition is the whole cache and is written as the output
+// itself.
 // The XCDs take the work groups in turn, so where P and 8 have a factor g in
 // common a partition number would stay on 8 / g of the XCDs, and the last
 // partitions, past most requests' lengths, would leave theirs idle: the
@@ -106,7 +108,8 @@ __device__ __forceinline__ float row_sum(float x) {
 // partitions (8 x 32 x 260..520 keys) took 15.4 us against 13.9 in grid order.
 // Bound by reading K and V; the loads in flight come from the resident work
 // groups (four per compute unit), so no stage is requested ahead of another.
-__global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
+template <int ST, int POL>
+__global__ __launch_bounds__(kNT, ST > kStage ? 2 : 4) void attn_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, const int32_t* __restrict__ lens, int32_t heads,
     int64_t max_len, float scale, int32_t P, int32_t CH, float* __restrict__ m_out,
@@ -139,23 +142,23 @@ __global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
 
   float m = -INFINITY, sum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int t0 = lo + g; t0 - g < hi; t0 += kStageKeys) {
-    uint4 kreg[kStage], vreg[kStage];
+  for (int t0 = lo + g; t0 - g < hi; t0 += ST * kGroups) {
+    uint4 kreg[ST], vreg[ST];
 #pragma unroll
-    for (int j = 0; j < kStage; ++j) {
+    for (int j = 0; j < ST; ++j) {
       const int t = t0 + kGroups * j;             // keys past hi read zero
-      kreg[j] = bld16(kr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
+      kreg[j] = bld16<POL>(kr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
     }
 #pragma unroll
-    for (int j = 0; j < kStage; ++j) {
+    for (int j = 0; j < ST; ++j) {
       const int t = t0 + kGroups * j;
-      vreg[j] = bld16(vr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
+      vreg[j] = bld16<POL>(vr, t < hi ? (t * kD + 8 * e) * 2 : kPastEnd);
     }
     // step 1: scores, each summed over the sixteen lanes of its key
-    float s[kStage];
+    float s[ST];
     float mn = m;
 #pragma unroll
-    for (int j = 0; j < kStage; ++j) {
+    for (int j = 0; j < ST; ++j) {
       float kf[8];
       unpack8(kreg[j], kf);
       float d = 0.f;
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(kNT, 4) void attn_partial_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= c;
 #pragma unroll
-    for (int j = 0; j < kStage; ++j) {
+    for (int j = 0; j < ST; ++j) {
       const float w = expf(s[j] - ms);            // 0 for keys past hi
       sum += w;
       float vf[8];
@@ -360,7 +363,28 @@ int32_t partitions(int64_t max_len, int32_t CH) {
 // 31.6).
 int32_t decode_chunk(int32_t batch, int32_t heads, int64_t max_len) {
   const int64_t groups = (int64_t)batch * heads * partitions(max_len, 2 * kC);
-  return max_len <= 2 * kC || groups >= 24 * 256 ? 2 * kC : kC;
+  return max_len <= 2 * kC || groups >= 24 * kCUs ? 2 * kC : kC;
+}
+
+// Whether K and V are read with the default cache policy, so that a cache that
+// fits the L2s (32 MB in all) may still be there in the next step, or
+// non-temporally: up to 48 MB.  (us per step over one cache, default against
+// non-temporal: 8 requests x 8 heads x 600 keys, 20 MB, 8.7 and 9.2; 16 x 8 x
+// 600, 39 MB, 10.7 and 12.0; 8 x 32 x 520, 68 MB, 14.2 and 13.9; 64 x 4 x 600,
+// 79 MB, 16.1 and 15.5.  A plain read of 2.4 GB runs at 6.3 TB/s by default
+// and at 7.1 non-temporally.)
+bool keep_cached(int32_t batch, int32_t heads, int64_t max_len) {
+  return (int64_t)batch * heads * max_len * (2 * kD * 2) <= (48 << 20);
+}
+
+// Whether a partition of kC keys is one stage: where the launch has more work
+// groups than are resident at once, a wavefront's second stage is a trip that
+// other work groups could have used (128 x 8 x 350..700 keys, 3072 work groups:
+// 47.9 us in two stages, 46.4 in one; 16 x 16 x 800..1600, 1792: 30.4 and
+// 29.6); below that the smaller kernel is as fast or faster (64 x 4 x 300..600,
+// 768: 14.8 and 15.5; 16 x 8 x 1000..2000, 1024: 20.8 and 21.5).
+bool whole_stage(int32_t batch, int32_t heads, int32_t P, int32_t CH) {
+  return CH == kC && (int64_t)batch * heads * P > 4 * kCUs;
 }
 
 plora_status run_partial(const uint16_t* q, const uint16_t* k, const uint16_t* v,
@@ -371,9 +395,12 @@ plora_status run_partial(const uint16_t* q, const uint16_t* k, const uint16_t* v
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o))
     return PLORA_ERR_UNSUPPORTED;
   const int32_t P = partitions(max_len, CH);
+  auto* kernel = keep_cached(batch, heads, max_len) ? attn_partial_kernel<kStage, kCached>
+                 : whole_stage(batch, heads, P, CH) ? attn_partial_kernel<kWholeStage, kOnce>
+                                                    : attn_partial_kernel<kStage, kOnce>;
   (void)hipGetLastError();
-  hipLaunchKernelGGL(attn_partial_kernel, dim3(P, heads, batch), dim3(kNT), 0, stream, q, k,
-                     v, lens, heads, max_len, scale, P, CH, m, l, o, out);
+  hipLaunchKernelGGL(kernel, dim3(P, heads, batch), dim3(kNT), 0, stream, q, k, v,
+                     lens, heads, max_len, scale, P, CH, m, l, o, out);
   return launch_status();
 }
 

@@ -179,7 +179,11 @@ def test_llama7b_decode_shape(P):
     (256, 32, 300),      # one partition holds the cache: no merge
     (48, 32, 2100),      # partitions of 512 keys, the last one short
     (3, 1, 8500),        # 34 partitions: the wide merge, more than its 32 groups
-    (2, 1, 33),          # one partition of the short form, then the merge
+    (2, 1, 33),          # one stage holds the cache
+    (9, 8, 760),         # three partitions: the merge of a few; a cache the L2s hold
+    (20, 8, 1500),       # six partitions, turned by one after every four heads
+    (70, 8, 760),        # partitions of one stage, three per head
+    (6, 32, 1024),       # four full partitions
 ])
 def test_decode_partition_forms(P, Bn, H, Lmax):
     """The partitions plora_attn_decode takes by shape, against the
@@ -203,3 +207,28 @@ def test_decode_partition_forms(P, Bn, H, Lmax):
         check_out(pick(out), ref)
         if lens[b] == 0:
             assert (out[b] == 0).all()
+
+
+@pytest.mark.parametrize("Lmax", [
+    300,     # one partition: partials and a merge after all
+    700,     # three: the merge of a few
+    1300,    # six
+    8500,    # 34: the wide merge
+])
+def test_decode_into_unaligned_output(P, Lmax):
+    """An output that starts at an odd element takes the merge whatever the
+    partition count, and nothing around it is written."""
+    Bn, H = 3, 2
+    g = torch.Generator(device="cuda").manual_seed(Lmax)
+    mk = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, K, V = mk(Bn, H, D), mk(Bn, H, Lmax, D), mk(Bn, H, Lmax, D)
+    lens = np.array([Lmax, 0, min(Lmax, 257)], np.int32)
+    buf = torch.full((Bn * H * D + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = buf[17:17 + Bn * H * D].view(Bn, H, D)
+    ws = torch.empty(P.attn_workspace_bytes(Bn, H, Lmax), dtype=torch.uint8, device="cuda")
+    P.attn_decode(q, K, V, dev(lens), 0.09, out, ws)
+    torch.cuda.synchronize()
+    u16 = lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    check_out(u16(out), OA.attention(u16(q), u16(K), u16(V), lens, 0.09))
+    assert (out[1] == 0).all()
+    assert (buf[:17] == 7).all() and (buf[17 + Bn * H * D:] == 7).all()
