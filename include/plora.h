@@ -404,10 +404,11 @@ plora_status plora_pool_device_pointer(const void* host, const void** device);
  *   counts[1]  tokens that kept y_base because their adapter entry breaks
  *              the contract (a rank outside [0, max_rank], or a block
  *              misaligned or outside its array), counted once per call;
- *              plora_expand counts only when it is given a workspace.  A
- *              one-launch call (T <= 256) also skips and counts the tokens
- *              of a tile longer than PLORA_SMALL_BATCH_TILE_TOKENS, which
- *              plora_segment never writes for such a batch.
+ *              plora_expand counts only when it is given a workspace.  An
+ *              apply of T <= 256 tokens whose tiles are split among several
+ *              work groups also skips and counts the tokens of a tile longer
+ *              than PLORA_SMALL_BATCH_TILE_TOKENS, which plora_segment never
+ *              writes for such a batch.
  * PLORA_ERR_INVALID_ARG for null pointers, PLORA_ERR_WORKSPACE_TOO_SMALL for
  * a buffer that cannot be a workspace, PLORA_ERR_HIP for a failed copy.
  * Not for the hot path. */

@@ -14,11 +14,12 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_apply_kernel(Sma
   uint64_t ep = 0;
   if (X) ep = xload(g.xep + u);
   SmallItem<2> t;
-  const int L = small_tile(g, u, s, t);
+  int p0;
+  const int L = small_tile<!X>(g, u, s, t, p0);
   if (L == 0) return;
   small_ranges<2>(g, a.S, a.J, s, t);
   if (!X && t.j0 >= t.j1) return;
-  small_run<MAXL, X, DEEP>(g, t, L, &sm, s, a.S, u, ep);
+  small_run<MAXL, X, DEEP>(g, t, L, p0, &sm, s, a.S, u, ep);
 }
 
 // plora_shrink: item (tile, slice of h_in), as the apply's.  One slice writes
@@ -32,11 +33,11 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_shrink_kernel(Sm
   const int u = X ? (int)blockIdx.x / a.S : (int)blockIdx.x;
   const int s = X ? (int)blockIdx.x - u * a.S : 0;
   SmallItem<2> t2;
-  const int L = small_tile(g, u, s, t2);
+  int p0;
+  const int L = small_tile<true>(g, u, s, t2, p0);
   if (L == 0) return;
   small_ranges<2>(g, a.S, a.J, s, t2);
-  const int p0 = uni(g.tiles[u].y);
-  small_tokens<MAXL>(t2, L, [&](const auto& t, int l, bool) {
+  small_tokens<MAXL, true>(g, t2, L, p0, [&](const auto& t, int l, bool) {
     constexpr int TG = std::remove_reference_t<decltype(t)>::kTokens;
     SmallLds<TG>& sm = *reinterpret_cast<SmallLds<TG>*>(&smx);
     XRegs<TG> xr;
@@ -60,13 +61,13 @@ __global__ __launch_bounds__(kST) void small_gather_kernel(SmallArgs a) {
   const ApplyArgs& g = a.g;
   SmallItem<2> t;
   const int u = blockIdx.x;
-  const int L = small_tile(g, u, 1, t);       // (slice 0 of the shrink counted the skips)
+  int p0;
+  const int L = small_tile<true>(g, u, 1, t, p0);   // (slice 0 of the shrink counted the skips)
   if (L == 0) return;
-  const int p0 = uni(g.tiles[u].y);
   const int64_t step = (int64_t)g.T * g.max_rank;
   for (int o = threadIdx.x; o < L * t.r; o += kST) {
     const int l = o / t.r, c = o - l * t.r;
-    const int tk = l == 0 ? t.tok[0] : t.tok[1];
+    const int tk = l == 0 ? t.tok[0] : l == 1 ? t.tok[1] : tile_token(g, p0 + l);
     const float* src = g.vpart + (int64_t)(p0 + l) * g.max_rank + c;
     float p[kMaxSlices];
 #pragma unroll
@@ -87,11 +88,12 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_expand_kernel(Sm
   int u, s;
   small_slot<false>(blockIdx.x, a.J, a.gl, u, s);
   SmallItem<2> t2;
-  const int L = small_tile(g, u, s, t2);
+  int p0;
+  const int L = small_tile<true>(g, u, s, t2, p0);
   if (L == 0) return;
   small_ranges<2>(g, a.S, a.J, s, t2);
   if (t2.j0 >= t2.j1) return;
-  small_tokens<MAXL>(t2, L, [&](const auto& t, int l, bool) {
+  small_tokens<MAXL, true>(g, t2, L, p0, [&](const auto& t, int, bool) {
     constexpr int TG = std::remove_reference_t<decltype(t)>::kTokens;
     SmallLds<TG>& sm = *reinterpret_cast<SmallLds<TG>*>(&smx);
     BRegs<small_batch(DEEP)> br;

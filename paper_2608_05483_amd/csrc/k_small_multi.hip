@@ -23,11 +23,12 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_multi_kernel(Mul
   g.a_off = q.a_off; g.b_off = q.b_off; g.ranks = q.ranks; g.scales = q.scales;
   g.y = q.y; g.ldy = q.ldy; g.h_out = q.h_out; g.max_rank = q.max_rank;
   SmallItem<2> t;
-  const int L = small_tile(g, u, s, t);
+  int p0;
+  const int L = small_tile<!X>(g, u, s, t, p0);
   if (L == 0) return;
   small_ranges<2>(g, S, J, s, t);
   if (!X && t.j0 >= t.j1) return;
-  small_run<MAXL, X, DEEP>(g, t, L, &sm, s, S, slot, ep);
+  small_run<MAXL, X, DEEP>(g, t, L, p0, &sm, s, S, slot, ep);
 }
 
 void launch_small_multi(const MultiArgs& m, int32_t S, int32_t J, int32_t gl, int32_t deep,

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_block_kernel(Sma
   }
   small_ranges<2>(g, a.S, a.J, s, t);
   if (!X && t.j0 >= t.j1) return;
-  small_run<2, X, DEEP>(g, t, L, &sm, s, a.S, u, ep);
+  small_run<2, X, DEEP>(g, t, L, p0, &sm, s, a.S, u, ep);
 }
 
 void launch_small_segment_apply(const SmallArgs& a, const int32_t* idx, const SegOut& so,

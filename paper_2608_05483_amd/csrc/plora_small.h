@@ -811,27 +811,39 @@ __device__ __forceinline__ void small_body(const ApplyArgs& g, const SmallItem<T
   expand_small<TG, SU>(g, t, sm, br, yr);
 }
 
-// Tile u of the segmentation: its record, tokens and adapter.  0: nothing
-// to do, 1 or 2: tokens.  A tile longer than kSmallTile is skipped and
-// counted like an unusable entry (plora_segment never writes one for a
-// batch this small).
-__device__ __forceinline__ int small_tile(const ApplyArgs& g, int u, int s, SmallItem<2>& t) {
+// The token at position p of the segmentation, -1 for none.
+__device__ __forceinline__ int tile_token(const ApplyArgs& g, int p) {
+  const int t = g.perm[p];
+  return t >= 0 && t < g.T ? t : -1;
+}
+
+// Tile u of the segmentation: its record, first two tokens and adapter.  0:
+// nothing to do, else its tokens, from position p0.  plora_segment writes no
+// tile longer than kSmallTile for a batch this small, but a caller's own list
+// may: ANY takes tiles of up to kTT tokens; without it (the exchange regions
+// hold kSmallTile tokens) a longer one is skipped and counted like an unusable
+// entry.
+template <bool ANY>
+__device__ __forceinline__ int small_tile(const ApplyArgs& g, int u, int s, SmallItem<2>& t,
+                                          int& p0) {
+  p0 = 0;
   if (u >= g.tile_cap) return 0;
   const int4 ti = g.tiles[u];
   if (ti.x < 0 || ti.x >= g.N || ti.z <= 0 || ti.z > kTT || ti.y < 0 || ti.y + ti.z > g.T)
     return 0;
-  const int a = uni(ti.x), p0 = uni(ti.y), L = uni(ti.z);
-  int t0 = uni(g.perm[p0]), t1 = uni(g.perm[p0 + (L > 1 ? 1 : 0)]);
+  const int a = uni(ti.x), L = uni(ti.z);
+  p0 = uni(ti.y);
+  const int t0 = uni(tile_token(g, p0)), t1 = uni(tile_token(g, p0 + (L > 1 ? 1 : 0)));
   const int r = uni(g.ranks[a]);
   const int64_t ao = g.a_off[a], bo = g.b_off[a];
   const float sc = g.scales[a];
-  t.tok[0] = t0 >= 0 && t0 < g.T ? t0 : -1;
-  t.tok[1] = L > 1 && t1 >= 0 && t1 < g.T ? t1 : -1;
+  t.tok[0] = t0;
+  t.tok[1] = L > 1 ? t1 : -1;
   bool bad;
   const bool ok = small_adapter<2>(g, r, sc, ao, bo, t, bad);
-  if (!ok || L > kSmallTile) {
-    if ((bad || L > kSmallTile) && s == 0 && g.count_skips && !(r == 0 && L <= kSmallTile))
-      bump(g, 1, (unsigned long long)L);
+  const bool fits = ANY || L <= kSmallTile;
+  if (!ok || !fits) {
+    if ((bad || !fits) && s == 0 && g.count_skips) bump(g, 1, (unsigned long long)L);
     return 0;
   }
   return L;
@@ -848,35 +860,38 @@ __device__ __forceinline__ SmallItem<TG> narrow(const SmallItem<2>& t) {
 }
 
 // The item's tokens through f(item of TG tokens, first row of the tile,
-// whether it is the last): a kernel of single-token tiles (MAXL = 1) takes a
-// longer tile, which only a caller's own tile list can hold, token by token.
-template <int MAXL, class F>
-__device__ __forceinline__ void small_tokens(const SmallItem<2>& t2, int L, F&& f) {
+// whether it is the last): two at once where the tile has two (MAXL = 2), else
+// one by one, which also serves the longer tiles of a caller's own list (ANY,
+// see small_tile; a loop over pairs spilled).
+template <int MAXL, bool ANY, class F>
+__device__ __forceinline__ void small_tokens(const ApplyArgs& g, const SmallItem<2>& t2, int L,
+                                             int p0, F&& f) {
   if constexpr (MAXL > 1) {
-    if (L > 1) {
+    if (L == 2) {
       f(narrow<2>(t2), 0, true);
       return;
     }
-    f(narrow<1>(t2), 0, true);
-  } else {
-    SmallItem<1> t = narrow<1>(t2);
-#pragma unroll 1
-    for (int l = 0; l < L; ++l) {
-      if (l > 0) {
-        t.tok[0] = t2.tok[1];
-        lds_sync();
-      }
-      f(t, l, l == L - 1);
+    if constexpr (!ANY) {
+      f(narrow<1>(t2), 0, true);
+      return;
     }
+  }
+  SmallItem<1> t = narrow<1>(t2);
+#pragma unroll 1
+  for (int l = 0; l < L; ++l) {
+    if (l > 0) {
+      t.tok[0] = ANY ? uni(tile_token(g, p0 + l)) : t2.tok[1];
+      lds_sync();
+    }
+    f(t, l, l == L - 1);
   }
 }
 
-
 // A whole item of L tokens: x is requested first.
 template <int MAXL, bool X, bool DEEP>
-__device__ __forceinline__ void small_run(const ApplyArgs& g, const SmallItem<2>& t2, int L,
+__device__ __forceinline__ void small_run(const ApplyArgs& g, const SmallItem<2>& t2, int L, int p0,
                                           void* lds, int s, int S, int slot, uint64_t ep) {
-  small_tokens<MAXL>(t2, L, [&](const auto& t, int l, bool last) {
+  small_tokens<MAXL, !X>(g, t2, L, p0, [&](const auto& t, int l, bool last) {
     constexpr int TG = std::remove_reference_t<decltype(t)>::kTokens;
     SmallLds<TG>& sm = *reinterpret_cast<SmallLds<TG>*>(lds);
     XRegs<TG> xr;

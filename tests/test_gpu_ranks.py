@@ -224,8 +224,8 @@ def test_unusable_entries_are_counted(P, reps):
 
 
 def test_overlong_one_launch_tile_is_skipped_and_counted(P):
-    """A one-launch call (T <= 256) holds each tile's partial v in an
-    exchange region sized for PLORA_SMALL_BATCH_TILE_TOKENS tokens; a tile
+    """An apply whose tiles are split (T <= 256) holds each tile's partial v in
+    an exchange region sized for PLORA_SMALL_BATCH_TILE_TOKENS tokens; a tile
     longer than that (which plora_segment never writes for such a batch) is
     skipped, its tokens keep y_base and are counted, and every other tile
     gives the bits of the unmodified segmentation."""
@@ -253,6 +253,48 @@ def test_overlong_one_launch_tile_is_skipped_and_counted(P):
     assert (y[rest] == y_ref[rest]).all()
     give_ups, n_skipped = run.ws.counters()
     assert give_ups == 0 and n_skipped == L
+
+
+LONG_TILES = [
+    # T, h_in, h_out, ranks, N, longest tile, whether the apply takes one slice
+    (40, 4096, 512, (16, 5), 3, 32, True),      # single-token tiles otherwise
+    (200, 4096, 520, (8, 64, 12), 9, 31, True),
+    (200, 2048, 2048, (8, 128, 12), 9, 5, False),
+    (256, 4096, 1024, (3, 16), 7, 32, False),   # deep slices
+]
+
+
+@pytest.mark.parametrize("T,h_in,h_out,ranks,N,longest,one_slice", LONG_TILES)
+def test_longer_tiles_of_a_callers_list(P, monkeypatch, T, h_in, h_out, ranks, N, longest,
+                                        one_slice):
+    """A caller's own tile list may hold tiles of up to PLORA_TILE_TOKENS
+    tokens for a small batch too: the split calls, and an apply whose tiles
+    are not split, run them to the oracle's bars and count nothing."""
+    monkeypatch.setitem(W.CONFIGS, "long",
+                        W.ConfigShape(T, N, h_in, h_out, 8, "uniform", scale=(0.5, 1.0, 2.0)))
+    rng = np.random.default_rng(T + h_in)
+    idx = rng.integers(0, N, size=T).astype(np.int32)
+    idx[1], idx[2] = -1, N + 1
+    w = W.make_workload("long", seed=78, scale="parity", idx=idx, ranks=np.resize(ranks, N))
+    say(f"longer tiles T={T} h_in={h_in} h_out={h_out} ranks={ranks} up to {longest}")
+    run = Run(P, w).segment()
+    n_seg = int(run.segs.meta[0].item())
+    ptr, ids = run.segs.seg_ptr.cpu().numpy(), run.segs.seg_id.cpu().numpy()
+    new = [(ids[k], p, min(longest, ptr[k + 1] - p), k) for k in range(n_seg)
+           for p in range(ptr[k], ptr[k + 1], longest)]
+    assert max(t[2] for t in new) > P.PLORA_SMALL_BATCH_TILE_TOKENS
+    tiles = np.tile(np.array([-1, 0, 0, -1], np.int32), (run.segs.tiles.numel() // 4, 1))
+    tiles[:len(new)] = new
+    run.segs.tiles.copy_(torch.from_numpy(tiles.reshape(-1)))
+    run.segs.meta[4] = len(new)
+    yref, yout = oracle_y(w)
+    v = run.shrink()
+    check_v(w, v.cpu().numpy(), w.idx)
+    y = run.expand(v)
+    check_y(y, yref, yout, w, strict_l2=True)
+    if one_slice:
+        assert (run.apply() == y).all()
+    check_counters(run)
 
 
 SMALL_EDGES = [
