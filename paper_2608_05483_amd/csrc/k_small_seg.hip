@@ -1,20 +1,19 @@
 // k_small_seg.hip -- plora_segment_apply of batches of up to kSegApplyMax
-// tokens in one launch.
+// tokens in one launch, the tiles' slices exchanging (see
+// segment_apply_one_launch).
 #include "plora_small.h"
 
 namespace plora_impl {
 
-template <bool X, bool DEEP>
+template <bool DEEP>
 __device__ __forceinline__ void direct_item(const SmallArgs& a, const ApplyArgs& g,
                                             const int32_t* idx, int item, SmallLds<1>& sm) {
   int u, s;
-  small_slot<X>(item, a.J, a.gl, u, s);
+  small_slot<true>(item, a.J, a.gl, u, s);
   if (u >= g.T) return;
   SmallItem<1> t;
   small_ranges<1>(g, a.S, a.J, s, t);
-  if (!X && t.j0 >= t.j1) return;
-  uint64_t ep = 0;
-  if (X) ep = xload(g.xep + u);
+  const uint64_t ep = xload(g.xep + u);
   t.tok[0] = u;
   XRegs<1> xr;
   x_issue<1>(g, t.tok, t.k0, min(t.k1, t.k0 + kSXW), xr);
@@ -25,7 +24,7 @@ __device__ __forceinline__ void direct_item(const SmallArgs& a, const ApplyArgs&
     if (bad && s == 0 && g.count_skips) bump(g, 1, 1);
     return;
   }
-  small_body<1, X, DEEP>(g, t, xr, sm, s, a.S, u, ep);
+  small_body<1, true, DEEP>(g, t, xr, sm, s, a.S, u, ep);
 }
 
 // Up to kDecodeTokens tokens (single-token tiles): item (u, s) takes token u
@@ -34,7 +33,7 @@ __device__ __forceinline__ void direct_item(const SmallArgs& a, const ApplyArgs&
 // then its adapter's metadata.  Work group 0 only ranks the batch and writes
 // the segmentation for later calls; in a DEEP launch, whose items may fill
 // the chip, it takes an item first.
-template <bool X, bool DEEP>
+template <bool DEEP>
 __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_direct_kernel(SmallArgs a, const int32_t* idx,
                                                               SegOut so) {
   __shared__ __align__(16) union {
@@ -48,7 +47,7 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_direct_kernel(Sm
     if (threadIdx.x < 64) wave_segment(g, idx, so, sh.lt);
     return;
   }
-  direct_item<X, DEEP>(a, g, idx, item, sh.sm);
+  direct_item<DEEP>(a, g, idx, item, sh.sm);
   if (DEEP && blockIdx.x == 0) {
     lds_sync();
     if (threadIdx.x < 64) wave_segment(g, idx, so, sh.lt);
@@ -57,16 +56,15 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_direct_kernel(Sm
 // 65 to kSegApplyMax tokens (tiles of two): every work group ranks the batch
 // (reading the ids takes the trip the tile record would) and takes its own
 // tile; work group 0 also writes the segmentation.
-template <bool X, bool DEEP>
+template <bool DEEP>
 __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_block_kernel(SmallArgs a, const int32_t* idx,
                                                              SegOut so) {
   __shared__ __align__(16) SmallLds<2> sm;
   __shared__ __align__(16) LocalTile lt;
   const ApplyArgs& g = a.g;
   int u, s;
-  small_slot<X>(blockIdx.x, a.J, a.gl, u, s);
-  uint64_t ep = 0;
-  if (X) ep = xload(g.xep + u);
+  small_slot<true>(blockIdx.x, a.J, a.gl, u, s);
+  const uint64_t ep = xload(g.xep + u);
   block_segment(g, idx, u, so, blockIdx.x == 0, lt);
   lds_sync();
   SmallItem<2> t;
@@ -84,20 +82,18 @@ __global__ __launch_bounds__(kST, small_waves(DEEP)) void small_block_kernel(Sma
     return;
   }
   small_ranges<2>(g, a.S, a.J, s, t);
-  if (!X && t.j0 >= t.j1) return;
-  small_run<2, X, DEEP>(g, t, L, p0, &sm, s, a.S, u, ep);
+  small_run<2, true, DEEP>(g, t, L, p0, &sm, s, a.S, u, ep);
 }
 
 void launch_small_segment_apply(const SmallArgs& a, const int32_t* idx, const SegOut& so,
                                 unsigned grid, hipStream_t stream) {
-  small_variant(a.g.T, a.S > 1, a.deep, [&](auto l, auto x, auto d) {
-    if constexpr (l() == 1)
-      hipLaunchKernelGGL((small_direct_kernel<x(), d()>), dim3(grid), dim3(kST), 0, stream, a,
-                         idx, so);
-    else
-      hipLaunchKernelGGL((small_block_kernel<x(), d()>), dim3(grid), dim3(kST), 0, stream, a,
-                         idx, so);
-  });
+  if (a.g.T <= kDecodeTokens) {
+    hipLaunchKernelGGL(a.deep ? small_direct_kernel<true> : small_direct_kernel<false>, dim3(grid),
+                       dim3(kST), 0, stream, a, idx, so);
+  } else {
+    hipLaunchKernelGGL(a.deep ? small_block_kernel<true> : small_block_kernel<false>, dim3(grid),
+                       dim3(kST), 0, stream, a, idx, so);
+  }
 }
 
 }  // namespace plora_impl

@@ -252,10 +252,12 @@ plora_status prepare(const plora_adapters* ad, const plora_segments* seg, void* 
 // longer than its chain of latencies: its kernels keep twice the chunks in
 // flight, two work groups per compute unit, and it is better not split
 // further (256 tokens at rank 64: 182 us per step, 192 split in three).  With
-// one slice (small h, or more slots than exchange regions) a work group computes
-// its tile's v whole.  The kernels stage a slice's x in LDS, so h_in above kSXW
+// one slice (h_in, or the narrowest output of the launch, below 1024) a work
+// group computes its tile's v whole.  The kernels stage a slice's x in LDS, so h_in above kSXW
 // sets the fewest slices; slices longer than that (h_in above 8 kSXW) are deep,
 // since max_rank is at least 8, and the deep kernels go on window by window.
+// (The slots are at most kXSlots: a batch this small has at most 256 tiles, and
+// plora_apply_multi sees to its sum.)
 constexpr int kSmallTarget = 768, kDeepTarget = 512;
 constexpr int64_t kDeepBytes = 128 * 1024;
 
@@ -271,22 +273,20 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
   p.slots = (cap + (1 << p.gl) - 1) >> p.gl << p.gl;
   const int s_min = std::min<int>(kMaxSlices, (h_in + kSXW - 1) / kSXW);
   auto slices = [&](int target) {
-    if (p.slots > kXSlots && s_min <= 1) return 1;
     return std::max(s_min, std::min(slice_limit(h_in, h_out), (target + p.slots / 2) / p.slots));
   };
   p.S = std::max(1, slices(kSmallTarget));
   p.deep = (int64_t)h_in * max_rank * 2 / p.S > kDeepBytes;
   if (p.deep) p.S = std::max(1, slices(kDeepTarget));
   // one slice of h_in: the work groups of a tile's column slices each compute
-  // v whole (h_in is small: 5 tokens, 792 -> 4512, rank 64, 12.5 us, 21.5
-  // undivided)
-  p.J = p.S > 1 || p.slots > kXSlots ? p.S
-        : std::max(1, std::min(h_out / kMinSlice, kSmallTarget / p.slots));
+  // v whole (5 tokens, 792 -> 4512, rank 64: 12.5 us, 21.5 undivided)
+  p.J = p.S > 1 ? p.S : std::max(1, std::min(h_out / kMinSlice, kSmallTarget / p.slots));
   return p;
 }
 
 // plora_segment_apply runs as one launch for batches of up to kSegApplyMax
-// tokens whose tiles can be split (words (key << tbits) | t with key <= N + 1
+// tokens whose tiles can be split: at most 256 slots, so small_plan then takes
+// two slices or more, and its kernels always exchange (words (key << tbits) | t with key <= N + 1
 // and tbits 6 up to 64 tokens, 8 above; tokens without an adapter read
 // adapter 0's metadata, so N >= 1).
 bool segment_apply_one_launch(int32_t T, const plora_adapters* ad) {
@@ -586,9 +586,6 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
   if (!aligned16(ws)) return PLORA_ERR_UNSUPPORTED;
   if (ws_bytes < l.total) return PLORA_ERR_WORKSPACE_TOO_SMALL;
   const int cap = seg->tile_cap <= 8 ? seg->tile_cap : (seg->tile_cap + 7) & ~7;
-  int min_out = ads[0].h_out;
-  for (int p = 1; p < n_proj; ++p) min_out = std::min(min_out, ads[p].h_out);
-  const SmallPlan sp = small_plan(n_proj * cap, ads[0].h_in, min_out, max_rank);
   if (!fused_for(seg->T) || n_proj * cap > kXSlots) {
     // one projection after another (the launch overheads are small next to
     // batches this large)
@@ -598,6 +595,13 @@ plora_status plora_apply_multi(const uint16_t* x, int64_t ldx, const plora_adapt
     }
     return PLORA_OK;
   }
+  // (the narrowest projection's columns limit the slices of all.  One launch
+  // even where that leaves one slice: 7168 -> 7168, 896, 896 at rank 128, two
+  // layers, 1 and 40 tokens 166 and 236 us, one projection after another 311
+  // and 375 on the former kernels)
+  int min_out = ads[0].h_out;
+  for (int p = 1; p < n_proj; ++p) min_out = std::min(min_out, ads[p].h_out);
+  const SmallPlan sp = small_plan(n_proj * cap, ads[0].h_in, min_out, max_rank);
   MultiArgs m;
   memset(&m, 0, sizeof m);
   st = prepare(&ads[0], seg, ws, ws_bytes, m.g, true);

@@ -119,12 +119,6 @@ __device__ __forceinline__ void stg16nt(uint16_t* p, const uint4& v) {
   __builtin_nontemporal_store(u32x4_nt{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_nt*>(p));
 }
 
-// The 8-byte form of ldg16z.
-__device__ __forceinline__ uint2 ldg8z(const uint16_t* p, const uint16_t* safe, bool ok) {
-  const uint2 v = *reinterpret_cast<const uint2*>(ok ? p : safe);
-  return ok ? v : make_uint2(0, 0);
-}
-
 // An adapter block (A_i or B_i: n bf16 values at p) as a raw buffer
 // resource.  Loads through it are range-checked by the hardware: a lane
 // whose offset lies past the block reads zero and fetches nothing.  That
@@ -215,11 +209,9 @@ __device__ __forceinline__ uint4 bld16(Rsrc r, int64_t e, bool ok) {
 // x rows feeding the A operand and A_i read back transposed
 // (ds_read_b64_tr_b16) into the B operand; the four wavefronts' partial tiles
 // are summed by a fixed pairwise tree.  The expand computes D^T[j][token] =
-// sum_c B_i[c][j] v[token][c] with B_i column chunks staged in LDS and read
-// transposed into the A operand; v is split into bf16 high and low parts
-// (v = hi + lo to about 2^-17 relative) so that no intermediate is rounded
-// below fp32 accuracy.  Each lane then owns four consecutive y columns of one
-// token.
+// sum_c B_i[c][j] v[token][c], each wavefront alone on blocks of columns (see
+// expand_blocks); v is split into bf16 high and low parts (v = hi + lo to about
+// 2^-17 relative) so that no intermediate is rounded below fp32 accuracy.
 //
 // Every reduction has a fixed order that depends only on the tile and the
 // slice widths, so results are bitwise reproducible, and the split calls
@@ -564,20 +556,6 @@ __device__ __forceinline__ void prefetch_b(const ApplyArgs& g, const Tile& t, ui
   for (int j = 0; j < BP; ++j) bpre[j] = bld16(rb, e0 + j * bstep, col_ok && j < m.njb);
 }
 
-// This thread's y words (first column octet, row slot 0) of the tile's tokens.
-template <int TG>
-__device__ __forceinline__ void prefetch_y(const ApplyArgs& g, const Tile& t, const int* tok,
-                                           uint4 (&ypre)[TG]) {
-  const ExpandMap m = expand_map(t);
-  const bool ok = m.co0 < m.n_oct && m.rb == 0;
-  const uint16_t* safe = g.y + (int64_t)max(tok[0], 0) * g.ldy + t.j0;
-#pragma unroll
-  for (int tt = 0; tt < TG; ++tt) {
-    const int tk = (ok && tt < t.L) ? tok[tt] : -1;
-    ypre[tt] = ldg16z(g.y + (int64_t)tk * g.ldy + t.j0 + (int64_t)m.co0 * 8, safe, tk >= 0);
-  }
-}
-
 // One butterfly step over lane mask M on the first N of V values: the lane
 // whose mask bit is set keeps the upper half, the other the lower half, each
 // adding the half its partner sends.
@@ -653,13 +631,10 @@ __device__ __forceinline__ void fma_a(float (&val)[TG * 8], const uint4* a, cons
 
 // v of a tile of L <= TG tokens into sm.vs, for a rank t.r that is a
 // multiple of 8 and at most R = 8 R_OCT (R a power of two).  Loads are
-// requested in the order they are consumed: x of the window, the first AP
-// chunks of A_i and, with prefetch set, this thread's first BP chunks of B_i
-// and its y words.
+// requested in the order they are consumed: x of the window, then the first AP
+// chunks of A_i.
 template <int R_OCT, int TG>
-__device__ __forceinline__ void shrink_valu(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                            uint4 (&bpre)[bp_depth<TG>()],
-                                            uint4 (&ypre)[TG], bool prefetch) {
+__device__ __forceinline__ void shrink_valu(const ApplyArgs& g, const Tile& t, const Smem& sm) {
   constexpr int R = 8 * R_OCT;
   constexpr int V = TG * 8;
   constexpr int S = ilog2(64 / R_OCT);     // row-slot bits inside a wavefront
@@ -701,10 +676,6 @@ __device__ __forceinline__ void shrink_valu(const ApplyArgs& g, const Tile& t, c
 #pragma unroll
     for (int j = 0; j < AP; ++j)
       apre[j] = bld16(ra, ae + j * astep, oct_ok && j < nj);
-    if (prefetch && w0 == t.k0) {
-      prefetch_b<bp_depth<TG>()>(g, t, bpre);
-      prefetch_y<TG>(g, t, sm.tok, ypre);
-    }
 #pragma unroll
     for (int i = 0; i < XR; ++i) {
       const int c = tid + i * kNT;
@@ -809,12 +780,10 @@ __device__ __forceinline__ void fma_b(float (&d)[TG * 8], const uint4* b, const 
 }
 
 // y[tok, cols] = bf16(y + s * v B_i[:, cols]) for a tile of L <= TG tokens.
-// The first column batch uses the chunks of B_i and the y words fetched
-// before the shrink.
+// The first column batch's first rows of B_i come at once (prefetch_b).
 template <int TG>
 __device__ __forceinline__ void expand_valu(const ApplyArgs& g, const Tile& t, const Smem& sm,
-                                            const uint4 (&bpre)[bp_depth<TG>()],
-                                            const uint4 (&ypre)[TG], bool have_y) {
+                                            const uint4 (&bpre)[bp_depth<TG>()]) {
   constexpr int BP = bp_depth<TG>();
   const ExpandMap m = expand_map(t);
   const int n_oct = m.n_oct;
@@ -864,9 +833,8 @@ __device__ __forceinline__ void expand_valu(const ApplyArgs& g, const Tile& t, c
 #pragma unroll
       for (int tt = 0; tt < TG; ++tt) {
         const int tk = tt < t.L ? sm.tok[tt] : -1;
-        yv[tt] = (have_y && cb == 0) ? ypre[tt]
-                 : ldg16z(g.y + (int64_t)tk * g.ldy + jc,
-                          g.y + (int64_t)max(sm.tok[0], 0) * g.ldy + jc, tk >= 0);
+        yv[tt] = ldg16z(g.y + (int64_t)tk * g.ldy + jc,
+                        g.y + (int64_t)max(sm.tok[0], 0) * g.ldy + jc, tk >= 0);
       }
       // every token's words first, then the stores (as in the matrix path:
       // a y word used after a store would make the compiler wait for it)
@@ -969,28 +937,25 @@ __device__ __forceinline__ int64_t xword(int o, int q) {
   return (int64_t)(o >> 3) * (8 * kMaxSlices) + q * 8 + (o & 7);
 }
 
-// A tile's pass: shrink (v of rows [k0, k1) into sm.vs), expand (columns
-// [j0, j1) from sm.vs), or both; with both, the expand's first loads of
-// B_i and y are requested with the shrink's.
+// A tile's pass: shrink (v of rows [k0, k1) into sm.vs) or expand (columns
+// [j0, j1) from sm.vs).
 template <int TG>
 __device__ __forceinline__ void valu_tile_tg(const ApplyArgs& g, const Tile& t, const Smem& sm,
                                              bool do_shrink, bool do_expand) {
-  uint4 bpre[bp_depth<TG>()], ypre[TG];
-#pragma unroll
-  for (int i = 0; i < TG; ++i) ypre[i] = make_uint4(0, 0, 0, 0);
-  const bool have_y = do_shrink;
   if (do_shrink) {
     switch (rank_class(t.r)) {
-      case 8: shrink_valu<1, TG>(g, t, sm, bpre, ypre, do_expand); break;
-      case 16: shrink_valu<2, TG>(g, t, sm, bpre, ypre, do_expand); break;
-      case 32: shrink_valu<4, TG>(g, t, sm, bpre, ypre, do_expand); break;
-      case 64: shrink_valu<8, TG>(g, t, sm, bpre, ypre, do_expand); break;
-      default: shrink_valu<16, TG>(g, t, sm, bpre, ypre, do_expand); break;
+      case 8: shrink_valu<1, TG>(g, t, sm); break;
+      case 16: shrink_valu<2, TG>(g, t, sm); break;
+      case 32: shrink_valu<4, TG>(g, t, sm); break;
+      case 64: shrink_valu<8, TG>(g, t, sm); break;
+      default: shrink_valu<16, TG>(g, t, sm); break;
     }
-  } else {
-    prefetch_b<bp_depth<TG>()>(g, t, bpre);
   }
-  if (do_expand) expand_valu<TG>(g, t, sm, bpre, ypre, have_y);
+  if (do_expand) {
+    uint4 bpre[bp_depth<TG>()];
+    prefetch_b<bp_depth<TG>()>(g, t, bpre);
+    expand_valu<TG>(g, t, sm, bpre);
+  }
 }
 
 __device__ __forceinline__ void valu_tile(const ApplyArgs& g, const Tile& t, const Smem& sm,
