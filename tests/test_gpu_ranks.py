@@ -2,11 +2,13 @@
 evaluation of section VII-A draws from {8, 16, 32, 64, 128}): every rank
 from 1 to 128 must give the oracle's y, through every form of the apply.
 
-Ranks that are multiples of 8 run the vector and matrix-core paths of the
-next power of two with their own row stride; the others take the LDS-staged
-shrink.  The batches below mix segment lengths so that one call exercises
-single-token tiles, the vector path's token widths 1, 2 and 4, matrix-path
-tiles of one and two 16-token tiles, and segments split over several tiles.
+Batches of up to 256 tokens stream A_i whatever the rank, in tiles of one or
+two tokens.  Above, ranks that are multiples of 8 run the vector and
+matrix-core paths of the next power of two with their own row stride, and the
+others take the LDS-staged shrink; the mixed segment lengths, taken twice,
+make one such call exercise the vector path's token widths 1, 2 and 4,
+matrix-path tiles of one and two 16-token tiles, and segments split over
+several tiles.
 Bars are those of test_gpu_parity (the benchmark spec's tolerance, the rigorous
 fp32 bound against float64, agreement with the oracle's bf16, and the
 relative L2 error of the delta on unit-scale inputs), plus: no exchange
@@ -104,6 +106,26 @@ def test_rank_matches_oracle_in_every_form(P, r):
     check_y(yd, ydr, ydo, wd, strict_l2=True)
     assert (rd.segment_apply() == yd).all()
     check_counters(rd)
+
+
+@pytest.mark.parametrize("r", RANKS)
+def test_rank_two_part_mixed_lengths(P, r):
+    """The same lengths twice over (350 tokens): the two-part form's vector,
+    matrix and general-rank paths at every rank, and the split calls."""
+    rng = np.random.default_rng(150 + r)
+    N = 64
+    idx = lengths_idx(rng, N, LENGTHS * 2)
+    w = W.make_workload("decode", scale="parity", ranks=r, n_adapters=N, idx=idx)
+    say(f"rank {r} two-part, mixed lengths: T={w.T}")
+    assert w.T > 256
+    run = Run(P, w).segment()
+    y = run.apply()
+    yref, yout = oracle_y(w)
+    check_y(y, yref, yout, w, strict_l2=True)
+    v = run.shrink()
+    check_v(w, v.cpu().numpy(), w.idx)
+    assert (run.expand(v) == y).all()
+    check_counters(run)
 
 
 @pytest.mark.parametrize("r", [3, 12, 48, 100, 128])
@@ -348,4 +370,44 @@ def test_small_batch_edges(P, monkeypatch, T, h_in, h_out, ranks, N):
     for p, yy in zip((w, w2), ys):
         pref, pout = oracle_y(p)
         check_y(bits16(yy), pref, pout, p, strict_l2=True)
+    assert ws.counters() == (0, 0)
+
+
+@pytest.mark.parametrize("T", [1, 8, 64, 200])
+@pytest.mark.parametrize("h_in,h_outs,ranks", [
+    (4096, (4096, 512, 512), (16, 64)),        # the narrow outputs leave one slice
+    (4096, (4096, 1032, 256), (5, 12)),
+    (8200, (2048, 512), (8, 128)),             # two slices at least, some without columns
+    (1024, (64, 4096), (16, 100)),             # a projection of one line
+])
+def test_apply_multi_of_mixed_widths(P, monkeypatch, T, h_in, h_outs, ranks):
+    """Several projections whose outputs differ in width, as grouped-query
+    layers have them, in one launch: each within the oracle's bars, and the
+    same bits twice."""
+    N = 12
+    rng = np.random.default_rng(T + h_in + len(h_outs))
+    idx = rng.integers(0, N, size=T).astype(np.int32)
+    if T > 2:
+        idx[1], idx[2] = -1, N + 1
+    say(f"apply_multi mixed T={T} h_in={h_in} h_outs={h_outs} ranks={ranks}")
+    ps = []
+    for k, h_out in enumerate(h_outs):
+        monkeypatch.setitem(W.CONFIGS, "mixed",
+                            W.ConfigShape(T, N, h_in, h_out, 8, "uniform", scale=(0.5, 1.0, 2.0)))
+        ps.append(W.make_workload("mixed", seed=79, scale="parity", idx=idx,
+                                  ranks=np.resize(ranks, N), stack_seed=k))
+    run = Run(P, ps[0]).segment()
+    ads = [P.Adapters.from_workload(p) for p in ps]
+    ws = P.Workspace(T, ads)
+    x = dev(np.ascontiguousarray(ps[0].x).view(np.int16))
+    got = []
+    for _ in range(2):
+        ys = [dev(np.ascontiguousarray(p.y_base).view(np.int16)) for p in ps]
+        P.apply_multi(x, ads, run.segs, ys, ws)
+        torch.cuda.synchronize()
+        got.append([bits16(y) for y in ys])
+    for p, a, b in zip(ps, *got):
+        pref, pout = oracle_y(p)
+        check_y(a, pref, pout, p, strict_l2=True)
+        assert (a == b).all()
     assert ws.counters() == (0, 0)
