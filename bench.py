@@ -362,7 +362,8 @@ class ApplyBench:
         one = self.one_launch() and not eager
         out["one_launch"] = one
         out["priced_s"] = step_s if one else out["apply_s"]
-        out["kernel"] = ("segment_apply_kernel (plora_segment_apply)" if one else
+        name = "small_direct_kernel" if self.w.T <= 64 else "small_block_kernel"
+        out["kernel"] = (name + " (plora_segment_apply)" if one else
                          "plora_apply" if self.n_proj == 1 else "plora_apply_multi")
         stem = ("plora_segment_apply_" if one else "plora_apply_") + self.name
         out["traffic"] = measured_traffic(stem) if self.n_proj == 1 else None

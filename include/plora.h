@@ -22,10 +22,9 @@
  *   plora_segment  group tokens by adapter id (stable counting sort)
  *   plora_shrink   v[t, :] = x[t, :] A_i            (E4's m = xA, fp32)
  *   plora_expand   y[t, :] += s_i v[t, :] B_i        (E4's y = mB)
- *   plora_apply    both: one launch for batches of up to 256 tokens, two
- *                  above (per-slice partial sums of v, fp32, pass through the
- *                  workspace; within the one launch too when a tile is
- *                  split among several work groups)
+ *   plora_apply    both in one launch, two for a tile capacity above 4096
+ *                  (per-slice partial sums of v, fp32, pass through the
+ *                  workspace when a tile is split among several work groups)
  *
  * Data types and layouts (all row-major, element strides):
  *   x       bf16 [T, ldx], first h_in columns used
@@ -141,8 +140,8 @@ typedef enum {
  * and matrix-core paths of the next power of two with their own row stride,
  * and other ranks (rows of A_i that are not 16-byte aligned) take an
  * LDS-staged shrink, correct but not tuned; smaller batches stream A_i as one
- * run of 16-byte chunks whatever the rank.  Offsets are multiples of 8 for every rank when h_in and h_out
- * are, as back-to-back blocks give.
+ * run of 16-byte chunks whatever the rank.  Offsets are multiples of 8 for
+ * every rank when h_in and h_out are, as back-to-back blocks give.
  */
 typedef struct {
   int32_t n_adapters;
@@ -301,8 +300,8 @@ plora_status plora_apply(const uint16_t* x, int64_t ldx,
  * first projection of a step, which also produces the step's segmentation
  * (seg is filled exactly as plora_segment fills it, so later projections and
  * layers can call plora_apply with it).  Arguments as for the two calls;
- * idx is int32 [T] device memory.  For T <= 256 in plora_apply's split
- * exchange form (and 1 <= N < 2^26 - 1 up to 64 tokens, N < 2^24 - 1 above)
+ * idx is int32 [T] device memory.  For T <= 256 with h_in and h_out of at
+ * least 1024 (and 1 <= N < 2^26 - 1 up to 64 tokens, N < 2^24 - 1 above)
  * this is one launch: above 64 tokens every work group segments the batch
  * itself (the grouping of section VI-B) and applies its own tile; up to 64
  * tokens (single-token tiles) every work group applies its own token
@@ -353,12 +352,12 @@ int32_t plora_segment_apply_launches(int32_t T, const plora_adapters* ad);
  * the ranks may differ), ys a host array of n_proj device pointers and ldys
  * a host array of their leading dimensions.  seg, ws and stream as for
  * plora_apply; ws must hold plora_workspace_bytes_multi(T, ads, n_proj)
- * bytes, zeroed once before its first use.  Batches small enough for the
- * split exchange of plora_apply run all projections in one launch (their
- * tiles share the work groups, and each tile gets fewer slices than one
- * projection's alone would, so the bits can differ from separate
- * plora_apply calls while meeting the same bounds); other batches run
- * plora_apply once per projection.  Bitwise deterministic (with the same
+ * bytes, zeroed once before its first use.  Batches of T <= 256 whose tile
+ * slots, n_proj times the tile capacity (rounded up to 8 above 8), are at most
+ * 336 run all projections in one launch (their tiles share the work groups,
+ * and are split differently from one projection's alone, so the bits can
+ * differ from separate plora_apply calls while meeting the same bounds);
+ * other batches run plora_apply once per projection.  Bitwise deterministic (with the same
  * exception as plora_apply).  Outputs must not overlap x or each other.
  * PLORA_ERR_INVALID_ARG for null arrays, n_proj < 1, stacks whose
  * n_adapters or h_in differ, or a leading dimension below its width;

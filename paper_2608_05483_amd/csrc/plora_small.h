@@ -20,8 +20,9 @@
 //
 // A tile is split over S work groups, each with its share of h_in and of the
 // columns, which trade their partial v through the workspace (see
-// exchange_small), so that A_i and B_i are read once; with S = 1 (small h, or
-// more tiles than exchange regions) a work group has the tile to itself.
+// exchange_small), so that each tile's A_i and B_i are read once; with S = 1
+// (h_in or h_out below 1024) a work group computes the tile's v whole, for all
+// of the columns or, where they are many, for a slice of them.
 //
 // What bounds them: a launch of little data is a chain of latencies (start,
 // ids or tile, adapter metadata, A_i, reduction, exchange, B_i, store: 9 us
@@ -34,8 +35,8 @@
 // exchange) were 2 to 5 us slower per launch at decode.  Steps over 7B-shaped
 // layers, before (rank classes, LDS-staged shrink for ranks that are no
 // multiple of 8) and now: 64 tokens at rank 16 149 -> 120 us; ranks 4 to 40,
-// 100 tokens, 13B widths 284 -> 105; ranks 64 and 128 at h = 8192, 45 tokens,
-// 223 -> 212; 256 tokens at rank 64 181 -> 179.
+// 100 tokens, 13B widths 284 -> 108; ranks 64 and 128 at h = 8192, 45 tokens,
+// 223 -> 212; 256 tokens at rank 64 as before, 182.
 #ifndef PLORA_SMALL_H
 #define PLORA_SMALL_H
 
@@ -57,7 +58,17 @@ __host__ __device__ constexpr int small_ahead(int su) { return su == 8 ? 8 : 4; 
 constexpr int kSXW = 8192;               // rows of x staged in LDS per window
 constexpr int kSOct = kST;               // most column octets per expand pass
 
-constexpr int kReadOnce = 2;             // adapter reads: non-temporal
+
+// Adapter reads are non-temporal: distinct adapters come from HBM, once.  That
+// holds also where column slices (S = 1) or an adapter's other tiles read a
+// block again, unless few adapters serve the whole batch.  us per call or step,
+// this and the default policy: 64 tokens, h = 4096, rank 16, Zipf, four layers
+// 119 and 126; 256 tokens at rank 64 332 and 363 (two layers); one slice, 792
+// -> 4512 at rank 64, each call on another stack of 1000 adapters, 64 tokens
+// 15.1 and 16.8, 256 tokens 32.7 and 36.5, of four adapters 15.6 and 12.0;
+// split calls of 256 tokens at rank 64 386 and 399 over 1000 adapters, 257 and
+// 225 over eight (eight calls each).
+constexpr int kReadOnce = 2;
 
 // The work of one item (values uniform over the work group).
 template <int TG>
@@ -369,7 +380,7 @@ __device__ __forceinline__ void expand_small(const ApplyArgs& g, const SmallItem
       p[1] = make_float4(d[tt][4], d[tt][5], d[tt][6], d[tt][7]);
     }
     lds_sync();
-    // output quads: at most TG per thread (TG 2^(lg + 1) <= TG 1024)
+    // output quads: at most 2 TG per thread (TG 2^(lg + 1) <= TG 512)
     constexpr int NQ = 2 * TG;
     uint2 out[NQ];
 #pragma unroll
@@ -643,7 +654,12 @@ __device__ __forceinline__ bool exchange_small(SmallLds<TG>& sm, int r, int s, i
 // The same with hook() run between the first poll's request and its use: the
 // loads it issues return behind the poll's (the vector-memory counter retires
 // in order; requested before the poll they would hold it up) and travel while
-// the partners' words are waited for.
+// the partners' words are waited for.  For the deep kernels, whose B_i,
+// requested with A_i, would hold up their long streams (256 tokens at rank 64,
+// two layers: 332 us, 346 with exchange_small and the early request).  The
+// short ones request B_i early and take exchange_small: with the hook two
+// layers at rank 16 took 44.2 us at one token (42.6 without), 48.0 at eight
+// (44.4), 85.9 at 100 (90.1), 161 at 256 (164).
 template <int TG, class H>
 __device__ __forceinline__ bool exchange_hooked(SmallLds<TG>& sm, int r, int s, int S,
                                                uint32_t tag, uint64_t* words, int polls,
@@ -707,7 +723,8 @@ __device__ __forceinline__ void plain_v_small(const ApplyArgs& g, const SmallIte
 
 // ---- items -----------------------------------------------------------------------
 
-// How a launch splits its tiles: S slices of h_in and J = S column slices.
+// How a launch splits its tiles: S slices of h_in and J column slices (J = S
+// where they exchange, S > 1).
 struct SmallArgs {
   ApplyArgs g;
   int32_t S, J;
@@ -903,8 +920,7 @@ __device__ __forceinline__ void small_run(const ApplyArgs& g, const SmallItem<2>
 // ---- the segmentation inside plora_segment_apply ------------------------------------
 
 // The function of plora_segment for 64 < T <= kSegApplyMax tokens by the whole
-// work group (thread t < 256 holds token t, then sorted position t; the other
-// half of the threads shares the ranking).  Words are (key << 8) | t; segment
+// work group (thread t holds token t, then sorted position t).  Words are (key << 8) | t; segment
 // and tile starts are found with each wavefront's ballots and combined across
 // the wavefronts through LDS (counts for the indices, the last and first start
 // for the segment that spans a wavefront boundary).  Each token's adapter
