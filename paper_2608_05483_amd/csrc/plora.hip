@@ -278,6 +278,28 @@ SmallPlan small_plan(int cap, int32_t h_in, int32_t h_out, int32_t max_rank) {
   p.S = std::max(1, slices(kSmallTarget));
   p.deep = (int64_t)h_in * max_rank * 2 / p.S > kDeepBytes;
   if (p.deep) p.S = std::max(1, slices(kDeepTarget));
+  // Fewer slices, by at most half, where that gives whole ones: rows that are
+  // whole batches of every thread at ranks that are powers of two, and a power
+  // of two of column octets, so that no thread of the expand is idle (100
+  // tokens, h = 4096: 7 slices of 640 columns leave 48 of 128 octets' threads
+  // idle).  us a call, whole and uneven slices, formerly: 100 tokens at rank 8
+  // 10.3 (4), 12.2 (7), 11.0; at 16 12.1, 13.6, 14.9; at 32 15.7, 18.0, 17.5;
+  // 256 tokens at rank 16 16.7 (2), 18.8 (3), 18.0.  Low ranks only: longer
+  // slices of mixed ranks wait for the longest (256 tokens of ranks 8 to 32, a
+  // step of four layers 352 in 2 and 341 in 3; 100 tokens of ranks 8 to 64, two
+  // layers 127 and 124), and other ranks have no whole batches (256 tokens of
+  // ranks 4 to 40 22.4 and 21.3).  Not where the slices are the most there may
+  // be: those batches have too few work groups as it is.
+  if (max_rank <= (p.S > 5 ? 32 : 16) && (max_rank & (max_rank - 1)) == 0 && !p.deep &&
+      p.S < slice_limit(h_in, h_out)) {
+    for (int q = p.S; q >= std::max(2, std::max(s_min, (p.S + 1) / 2)); --q) {
+      const int oct = h_out / (8 * q);
+      if (h_in % (256 * q) == 0 && h_out % (64 * q) == 0 && (oct & (oct - 1)) == 0) {
+        p.S = q;
+        break;
+      }
+    }
+  }
   // one slice of h_in: the work groups of a tile's column slices each compute
   // v whole (5 tokens, 792 -> 4512, rank 64: 12.5 us, 21.5 undivided)
   p.J = p.S > 1 ? p.S : std::max(1, std::min(h_out / kMinSlice, kSmallTarget / p.slots));

@@ -330,6 +330,10 @@ SMALL_EDGES = [
     (64, 17000, 1096, (6, 64, 2), 9),          # three slices at least
     (65, 1024, 2048, (12, 20, 8), 30),         # tiles of two tokens, one over
     (256, 4104, 4104, (7, 64, 96), 40),        # the largest small batch, deep
+    (6, 4096, 4096, (8, 24, 3), 4),            # half batches in shrink and expand
+    (100, 4096, 4096, (8, 16, 32), 60),        # whole slices: 4 instead of 7
+    (100, 5120, 5120, (16, 5), 60),            # 5 instead of 7
+    (256, 4096, 4096, (8, 1, 16), 120),        # 2 instead of 3
     (9, 8192, 512, (8, 13, 128), 5),           # one slice that fills the LDS window
     (5, 65536, 256, (8, 13), 3),               # eight full windows, slices without columns
     (3, 65544, 1032, (8, 13, 100), 3),         # slices of a window and 64 rows
